@@ -85,12 +85,12 @@ def _mac(c):
 
 
 def _tree_mac(c):
-    """Weights one sample's connected configurations cannot do without: a hidden unit or head row depends on the
-    positions before its own only, so it is needed once per distinct prefix.  The distinct prefixes of length t are
-    the holes and particles that single and double excitations leave among the first t positions."""
+    """Multiply-adds one sample's connected configurations cannot do without: a hidden unit of degree d is a
+    function of the first d positions, so its products with the weights that read it are needed once per distinct
+    prefix of length d.  The distinct prefixes are the holes and particles that single and double excitations
+    leave among the first positions."""
     n, h, L = 2 * c["orbitals"], c["width"], c["layers"]
     m = 1 + np.arange(h) % (n - 1)
-    le = np.searchsorted(np.sort(m), np.arange(n + 1), side="right")
     count = np.bincount(m, minlength=n + 1)
 
     def prefixes(t):
@@ -102,11 +102,11 @@ def _tree_mac(c):
 
     rows = float(_entries(c["orbitals"])) if not c["cutoff"] else 5000.0
     node = [min(rows, prefixes(t)) for t in range(n + 1)]
-    tot = sum(node[d] * count[d] * (d + (L - 1) * le[d]) for d in range(1, n))
-    tot += sum(node[t] * le[t] for t in range(n))
+    after = count[::-1].cumsum()[::-1]           # units of degree d and more
+    tot = sum(node[d] * (after[d] + count[d] * ((L - 1) * after[d] + n - d)) for d in range(1, n))
     if c["phase"]:
-        return tot + rows * ((n - 2) * h + (L - 1) * h * h + 4 * h)
-    return tot + rows * 4.0 * le[n - 2]
+        return float(tot + rows * ((n - 2) * h + (L - 1) * h * h + 4 * h))
+    return float(tot + 4.0 * sum(node[d] * count[d] for d in range(1, n - 1)))
 
 
 def _sector(orbitals):
