@@ -242,6 +242,10 @@ typedef struct nqs_plan nqs_plan;
 nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc* net,
                            int64_t max_batch, uint32_t flags, int64_t chunk_samples,
                            nqs_plan** out);
+/* Bytes a call on batch samples can use.  The last part holds the prefix states
+   of the connected-configuration forward (up to two workgroups per CU): calls
+   also take a workspace without all of it, and evaluate the same values with
+   fewer workgroups, or row by row. */
 nqs_status nqs_plan_workspace_size(const nqs_plan* plan, int64_t batch, size_t* bytes);
 /* Plan facts: per-sample entry bound, chunk size, dedup on/off, number of
    parameters. */
@@ -357,8 +361,9 @@ nqs_status nqs_energy_grad(nqs_plan* plan, const float* d_params, const uint64_t
    and results as nqs_energy_grad; d_flags (device uint32, may be NULL)
    receives the call's device error word (NQS_DEV_* bits), which the call
    clears at its start.  Fails with NQS_ERR_WORKSPACE_TOO_SMALL, before
-   anything is enqueued, when nqs_plan_workspace_size(plan, B) exceeds the
-   array (create the plan with a smaller max_batch or chunk).  Every call on
+   anything is enqueued, when the workspace that B samples need exceeds the
+   array (create the plan with a smaller max_batch or chunk); the prefix
+   states that nqs_plan_workspace_size adds for speed take what is left.  Every call on
    one GPU uses the same array: calls that overlap on that GPU (several
    streams or threads) race, so the caller orders them.  Not profiled. */
 #define NQS_NOALLOC_SCRATCH_BYTES (256u << 20)
@@ -372,7 +377,8 @@ nqs_status nqs_energy_grad_noalloc(nqs_plan* plan, const float* d_params, const 
    which must hold nqs_multi_workspace_size bytes.  The sample forwards of
    all instances are one work list, and so are the connected-configuration
    forwards of each chunk round (round r holds chunk r of every instance that
-   has one): one forward launch per round and per group of at most 8
+   has one) that run row by row (a network with the prefix-shared forward
+   takes launches of its own): one forward launch per round and per group of at most 8
    instances with equal precision, width and forward variant.  Enumeration,
    ratio-and-reduce, energy and gradient run per instance.  Each instance's
    results equal those of nqs_energy_grad on it alone. */
@@ -481,9 +487,11 @@ typedef struct {
   double  forward_ms;       /* sum of forward kernel durations                */
   double  forward_rows;     /* configurations evaluated by those launches     */
   double  forward_flops;    /* forward_rows * 2 * (unmasked weights per row)  */
-  double  forward_flops_executed;  /* forward_rows * MFMA flops issued per row
-                                      (masked tiles skipped, padding included;
-                                      NQS_BF16X3 counts each of its BF16 MFMAs) */
+  double  forward_flops_executed;  /* MFMA flops issued (masked tiles skipped,
+                                      padding included; NQS_BF16X3 counts each of
+                                      its BF16 MFMAs).  Connected configurations
+                                      share their common prefixes' work, so this
+                                      can be below forward_flops */
 } nqs_profile;
 nqs_status nqs_plan_profile(nqs_plan* plan, int enable);
 nqs_status nqs_plan_profile_read(nqs_plan* plan, void* d_ws, nqs_profile* out);

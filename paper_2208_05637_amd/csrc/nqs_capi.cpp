@@ -172,7 +172,10 @@ struct nqs_plan {
   bool two = false;        // phase_mode 1: modulus network g and phase network gp
   size_t packed_bytes = 0; // packed weights of g, then (two) of gp at packed_phase
   size_t packed_phase = 0;
+  bool tree = false;       // connected configurations take the prefix-shared forward
+  TreePlan tp{};
   double flops_alg_row = 0, flops_exec_row = 0;   // forward flops per configuration
+  double flops_exec_phase_row = 0;                // of the second, the separate phase network's
   // profiling
   struct Rec { hipEvent_t a, b; int kind; int slot; };   // kind 0 call, 1 eloc, 2 forward
   bool prof = false;
@@ -180,11 +183,11 @@ struct nqs_plan {
   int next_slot = 0;
 };
 
-constexpr int kProfSlots = 8192;
-
 struct WsLayout {
   size_t err, prof, geom, packed, wm, lps, eloc, energy, cnt, off, stmp, rpart, diag, xe, he, lpe, htab,
       eu, xu, nu, dfirst, drank, drtmp, htab2, lp2, lpn, src, nnew, bscratch, total;
+  size_t tree, full;   // the prefix tree's states come last: total is what a call needs, full what it can use
+  int tree_grid;       // workgroups of the prefix-shared forward the given workspace has states for
 };
 
 // Enumeration grid for chunks of S samples: R ranges of gper flip groups.
@@ -202,7 +205,7 @@ static WsLayout layout(const nqs_plan* p, int64_t B) {
   auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
   const int hs = p->ham->has_imag ? 2 : 1;
   L.err = take(256);
-  L.prof = take((size_t)kProfSlots * 8);
+  L.prof = take((size_t)2 * kProfSlots * 8);   // row counts, then the prefix-shared forwards' MFMA flops
   L.geom = take(2 * sizeof(Geom));
   L.packed = take(p->packed_bytes);
   L.wm = take((size_t)p->g.n_params * p->bw);
@@ -235,7 +238,23 @@ static WsLayout layout(const nqs_plan* p, int64_t B) {
   }
   L.bscratch = take((size_t)backward_scratch_elems(p->g, p->Sb) * p->bw);
   L.total = o;
+  L.tree = o;
+  L.tree_grid = 0;
+  if (p->tree) {
+    // two workgroups per CU, and no more than the chunk has smallest segments
+    L.tree_grid = (int)std::min<int64_t>(2 * std::max(p->ctx->cu_count, 1), (p->EC + 255) / 256);
+    take((size_t)L.tree_grid * p->tp.args.scratch_wg);
+  }
+  L.full = o;
   return L;
+}
+
+// A workspace of `bytes` (at least total) may hold states for fewer
+// workgroups; below an eighth of the CUs the row-by-row forward is faster.
+static void fit_tree(const nqs_plan* p, size_t bytes, WsLayout& L) {
+  if (!L.tree_grid || bytes >= L.full) return;
+  const int fits = (int)((bytes - L.tree) / (size_t)p->tp.args.scratch_wg);
+  L.tree_grid = fits >= std::min(L.tree_grid, p->ctx->cu_count / 8) ? fits : 0;
 }
 
 // group 0 is the empty flip
@@ -789,6 +808,7 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
     p->packed_phase = align256(p->packed_bytes);
     p->packed_bytes = p->packed_phase + packed_bytes_of(p->gp);
   }
+  p->tree = tree_plan(p->g, p->tp);
   {
     // unmasked weights per configuration (MADE masks) and MFMA work issued
     const int n = g.n, h = g.h;
@@ -816,17 +836,19 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
       fr += (long long)(g.L - 1) * g.ksh[nb];
     }
     for (int nb = 0; nb < g.NHB; ++nb) fr += g.kso[nb];
+    long long ph1 = 0, ph = 0;
     if (p->two) {
       const Geom& q = p->gp;
       for (int nb = 0; nb < q.NB; ++nb) {
-        fr1 += q.ks1[nb];
-        fr += (long long)(q.L - 1) * q.ksh[nb];
+        ph1 += q.ks1[nb];
+        ph += (long long)(q.L - 1) * q.ksh[nb];
       }
-      fr += q.kso[0];
+      ph += q.kso[0];
     }
     const double mult = g.prec == P_BF16X3 ? 3.0 : (g.prec == P_BF16W ? 2.0 : 1.0);
     const double mult1 = mult > 1.0 ? mult - 1.0 : 1.0;
-    p->flops_exec_row = 2.0 * g.TB * g.KSTEP * (mult1 * (double)fr1 + mult * (double)fr);
+    p->flops_exec_phase_row = 2.0 * g.TB * g.KSTEP * (mult1 * (double)ph1 + mult * (double)ph);
+    p->flops_exec_row = 2.0 * g.TB * g.KSTEP * (mult1 * (double)fr1 + mult * (double)fr) + p->flops_exec_phase_row;
   }
   *out = p;
   return NQS_OK;
@@ -842,12 +864,15 @@ nqs_status nqs_plan_profile_read(nqs_plan* p, void* ws, nqs_profile* out) {
   if (!p || !out) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
   memset(out, 0, sizeof(*out));
   HIP_TRY(hipStreamSynchronize(p->ctx->stream));
-  std::vector<long long> slots;
+  std::vector<long long> slots, issued;
   if (p->next_slot > 0) {
     if (!ws) return fail(NQS_ERR_INVALID_ARGUMENT, "workspace is NULL");
     WsLayout L = layout(p, 0);
     slots.resize(std::min(p->next_slot, kProfSlots));
+    issued.resize(slots.size());
     HIP_TRY(hipMemcpy(slots.data(), (char*)ws + L.prof, slots.size() * 8, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(issued.data(), (char*)ws + L.prof + (size_t)kProfSlots * 8, slots.size() * 8,
+                      hipMemcpyDeviceToHost));
   }
   for (auto& r : p->recs) {
     float ms = 0.f;
@@ -858,7 +883,13 @@ nqs_status nqs_plan_profile_read(nqs_plan* p, void* ws, nqs_profile* out) {
     else {
       out->forward_launches += 1;
       out->forward_ms += ms;
-      if (r.slot >= 0 && r.slot < (int)slots.size()) out->forward_rows += (double)slots[r.slot];
+      if (r.slot >= 0 && r.slot < (int)slots.size()) {
+        const double rows = (double)slots[r.slot];
+        out->forward_rows += rows;
+        // a separate phase network's rows run row by row beside the modulus network's tree
+        const double plain = rows * (issued[r.slot] ? p->flops_exec_phase_row : p->flops_exec_row);
+        out->forward_flops_executed += (double)issued[r.slot] + plain;
+      }
     }
   }
   std::vector<hipEvent_t> evs;   // records may share their start event
@@ -867,7 +898,6 @@ nqs_status nqs_plan_profile_read(nqs_plan* p, void* ws, nqs_profile* out) {
   evs.erase(std::unique(evs.begin(), evs.end()), evs.end());
   for (hipEvent_t e : evs) (void)hipEventDestroy(e);
   out->forward_flops = out->forward_rows * p->flops_alg_row;
-  out->forward_flops_executed = out->forward_rows * p->flops_exec_row;
   p->recs.clear();
   p->next_slot = 0;
   return NQS_OK;
@@ -876,7 +906,7 @@ nqs_status nqs_plan_profile_read(nqs_plan* p, void* ws, nqs_profile* out) {
 nqs_status nqs_plan_workspace_size(const nqs_plan* p, int64_t B, size_t* bytes) {
   if (!p || !bytes) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
   if (B < 0 || B > p->max_batch) return fail(NQS_ERR_INVALID_ARGUMENT, "batch %lld outside 0..%lld", (long long)B, (long long)p->max_batch);
-  *bytes = layout(p, B).total;
+  *bytes = layout(p, B).full;
   return NQS_OK;
 }
 
@@ -900,6 +930,7 @@ static nqs_status check_ws(const nqs_plan* p, int64_t B, void* ws, size_t ws_byt
   if (B < 0 || B > p->max_batch) return fail(NQS_ERR_INVALID_ARGUMENT, "batch %lld outside 0..%lld", (long long)B, (long long)p->max_batch);
   L = layout(p, B);
   if (ws_bytes < L.total) return fail(NQS_ERR_WORKSPACE_TOO_SMALL, "workspace %zu < %zu bytes", ws_bytes, L.total);
+  fit_tree(p, ws_bytes, L);
   return NQS_OK;
 }
 
@@ -937,8 +968,27 @@ static void forward_net(const nqs_plan* p, const void* packed, const uint64_t* x
                    out, nullptr, s);
 }
 
+// The same of connected configurations in the enumeration's order: down their
+// prefix tree where the plan has one and the workspace its states.
+static void forward_connected(const nqs_plan* p, void* ws, const WsLayout& L, const void* packed, const uint64_t* x,
+                              long long bound, const long long* d_count, double* out, long long* slot,
+                              hipStream_t s) {
+  if (!L.tree_grid) {
+    forward_net(p, packed, x, bound, d_count, out, slot, s);
+    return;
+  }
+  const int waves = forward_variant_waves(p->g.prec, p->g.h, p->variant);
+  const int rows = forward_variant_rows(p->g.prec, p->g.h, p->variant);
+  launch_tree_forward(p->g, p->tp, tree_head_ksplit(p->g, waves, rows), packed, x, bound, d_count, out, slot,
+                      at<void>(ws, L.tree), L.tree_grid, s);
+  if (p->two)
+    launch_forward(p->gp, p->variant, p->resident, p->ctx->cu_count, (const char*)packed + p->packed_phase, x, bound,
+                   d_count, out, nullptr, s);
+}
+
 static void forward_profiled(nqs_plan* p, void* ws, const WsLayout& L, const void* packed,
-                             const uint64_t* x, long long bound, const long long* d_count, double* out) {
+                             const uint64_t* x, long long bound, const long long* d_count, double* out,
+                             bool connected) {
   hipEvent_t a = prof_mark(p);
   long long* slot = nullptr;
   int si = -1;
@@ -946,8 +996,10 @@ static void forward_profiled(nqs_plan* p, void* ws, const WsLayout& L, const voi
     si = p->next_slot++;
     slot = at<long long>(ws, L.prof) + si;
     launch_fill_u64(slot, 0ull, 1, p->ctx->stream);   // a launch with no tiles leaves it at zero rows
+    launch_fill_u64(slot + kProfSlots, 0ull, 1, p->ctx->stream);
   }
-  forward_net(p, packed, x, bound, d_count, out, slot, p->ctx->stream);
+  if (connected) forward_connected(p, ws, L, packed, x, bound, d_count, out, slot, p->ctx->stream);
+  else forward_net(p, packed, x, bound, d_count, out, slot, p->ctx->stream);
   prof_close(p, a, 2, si);
 }
 
@@ -1023,11 +1075,11 @@ static nqs_status run_local_energy(nqs_plan* p, const float* params, const uint6
                                    double* eloc, void* ws, const WsLayout& L) {
   void* packed = at<void>(ws, L.packed);
   pack_net(p, params, packed, p->ctx->stream);
-  forward_profiled(p, ws, L, packed, x, B, nullptr, at<double>(ws, L.lps));
+  forward_profiled(p, ws, L, packed, x, B, nullptr, at<double>(ws, L.lps), false);
   for (int64_t c0 = 0, k = 0; c0 < B; c0 += p->S, ++k) {
     const int64_t Sc = std::min<int64_t>(p->S, B - c0);
     const ChunkFwd cf = enum_chunk(p, x, c0, Sc, k, ws, L);
-    forward_profiled(p, ws, L, packed, cf.x, cf.bound, cf.d_count, cf.out);
+    forward_profiled(p, ws, L, packed, cf.x, cf.bound, cf.d_count, cf.out, true);
     finish_chunk(p, cf, ws, L);
     reduce_chunk(p, c0, Sc, cf, ws, L, eloc);
   }
@@ -1155,7 +1207,7 @@ static nqs_status multi_layout(int n_inst, const nqs_instance* inst, std::vector
       return fail(NQS_ERR_INVALID_ARGUMENT, "instance %d: batch %lld outside 1..%lld", i, (long long)I.B,
                   (long long)I.plan->max_batch);
     base[i] = total;
-    total += align256(layout(I.plan, I.B).total);
+    total += align256(layout(I.plan, I.B).full);
   }
   return NQS_OK;
 }
@@ -1274,9 +1326,12 @@ nqs_status nqs_energy_grad_multi(int n_inst, const nqs_instance* inst, void* ws,
       c0s.push_back(c0);
       scs.push_back(Sc);
       cfs.push_back(cf);
-      add_segs(i, cf.x, cf.d_count, cf.out, cf.bound, ids, segs);
+      if (L[i].tree_grid)
+        forward_connected(p, W[i], L[i], at<void>(W[i], L[i].packed), cf.x, cf.bound, cf.d_count, cf.out, nullptr, s);
+      else
+        add_segs(i, cf.x, cf.d_count, cf.out, cf.bound, ids, segs);
     }
-    if (ids.empty()) break;
+    if (rid.empty()) break;
     launch_groups(ids, segs);
     for (size_t k = 0; k < rid.size(); ++k) {
       finish_chunk(inst[rid[k]].plan, cfs[k], W[rid[k]], L[rid[k]]);

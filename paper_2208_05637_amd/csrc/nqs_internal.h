@@ -79,6 +79,47 @@ void launch_reduce(long long S, int R, const long long* off, long long cap, cons
 void launch_energy(const double* eloc, const double* w, long long B, double* energy,
                    unsigned* err, hipStream_t s);
 
+// Prefix-shared forward of the connected configurations (kernels_tree.hip).
+// Level of the prefix tree: the units of blocks [ca, eb) are evaluated for
+// each distinct prefix of d positions, the chains of blocks [cb, NB) run over
+// blocks [ca, cb) into the state at byte st of the workgroup's scratch, and the
+// log-sigmoids of positions [ta, tb) are complete.  The last level's nodes are
+// the rows.
+constexpr int kTreeLevels = 4;
+constexpr int kProfSlots = 8192;   // profiled launches between two reads
+struct TreeLevel {
+  int ca, cb, eb, d, ta, tb;
+  long long st;
+  long long flops;   // MFMA flops of one tile
+};
+struct TreeArgs {
+  const void* packed;
+  const uint64_t* x;
+  const long long* d_count;   // nullable: then rows = bound
+  long long bound;
+  double* out;
+  long long* prof_slot;       // nullable: receives the row count, and kProfSlots further on the MFMA flops
+  char* scratch;              // scratch_wg bytes per workgroup
+  long long scratch_wg;
+  int nlev, ksplit, own_max, stage_ld;
+  TreeLevel lev[kTreeLevels];
+};
+struct TreePlan {
+  TreeArgs args;
+  size_t lds;
+};
+// Levels of the network's tree; false where it has none (a sampling order the
+// enumeration does not walk depth first, the dense phase network, a network of
+// too few blocks).
+bool tree_plan(const Geom& g, TreePlan& t);
+// k slices of the row-by-row forward's head with that workgroup shape.
+int tree_head_ksplit(const Geom& g, int waves, int rows);
+// log psi (modulus only for net_kind 1) of rows [0, min(*d_count, rows_bound))
+// of x, equal to launch_forward's logits with that shape's head slices.
+void launch_tree_forward(const Geom& g, const TreePlan& t, int ksplit, const void* packed, const uint64_t* x,
+                         long long rows_bound, const long long* d_count, double* out, long long* prof_slot,
+                         void* scratch, int grid, hipStream_t s);
+
 // backward: recompute the sample forward on S samples and accumulate the
 // gradient into grad (f64, flat parameter layout).  scratch holds
 // backward_scratch_elems(g, S) elements of the path's backward type
