@@ -3,6 +3,8 @@
 // (activations of connected configurations are never stored), the output
 // seeds are built from the local energies, and masked GEMMs propagate them to
 // every weight and bias.
+#include <algorithm>
+
 #include "nqs_internal.h"
 
 namespace nqs {
@@ -240,84 +242,225 @@ void launch_pack_fused(const Geom& g, const float* params, void* packed, hipStre
 }
 
 // ------------------------------------------------------------ small GEMM
-// C(i,j) = sum_k A(i,k) B(k,j) with A(i,k) = A[i*sa0 + k*sa1],
-// B(k,j) = B[k*sb0 + j*sb1]; 64x64 tiles, 256 threads, 4x4 per thread.
+// C(i,j) = sum_k A(i,k) B(k,j) in 64x64 tiles, 256 threads.  What is contiguous
+// in memory follows from the use: activations and seeds are rows of samples.
+//   E_FWD      relu(A B + bias)    A by k, B by k   (activations x weights^T)
+//   E_FWD_LIN  A B + bias          A by k, B by k
+//   E_STORE    A B                 A by k, B by j   (seeds x weights)
+//   E_ADD      C + A B             A by k, B by j
+//   E_GRAD     grad += A B         A by i, B by j   (seeds^T x activations, k = samples)
+// E_STORE and E_ADD take the derivative of the ReLU in front of C (act) along.
+//
+// E_GRAD sums over the samples.  They are cut into blocks of KBLK: a block's
+// products are summed by one chain in the path's type and the blocks in order
+// in FP64.  With room for the blocks' sums (part) every block is a workgroup of
+// its own and a second kernel adds them; without it one workgroup takes them
+// in turn.  Both give the same bits.  The sums are bound by how many workgroups
+// a [h][h] result has: one chain over 4,096 samples ran 64 workgroups at 512
+// units for 480 us (16 at 256 units, 485 us); blocks take 20 us (14 us) and
+// their reduction 6 us, and the FP32 chains are 16 times shorter.  The same
+// workgroups sum A over the samples for the biases (a kernel of 45 us before).
 enum Epi { E_FWD = 0, E_FWD_LIN = 1, E_STORE = 2, E_ADD = 3, E_GRAD = 4 };
 
 struct GemmArgs {
   int Mr, Nc, K;
-  const void* A; long long sa0, sa1;
-  const void* B; long long sb0, sb1;
+  const void* A; long long sa;   // stride of A's and B's rows in memory
+  const void* B; long long sb;
   void* C; long long ldc;
   const void* bias;        // E_FWD / E_FWD_LIN
-  double* grad; long long grad_off; int mask_kind; long long grad_ld;   // E_GRAD
+  const void* act;         // E_STORE / E_ADD: C is 0 where act (ldc) is not positive; nullptr: everywhere kept
+  double* grad; long long grad_off, bias_off; int mask_kind;   // E_GRAD: rows of Nc, biases
+  void* part;              // E_GRAD: sums of the blocks [nz][Mr][Nc], then of A over the block [nz][Mr] FP64
+  int z0, nz;              // E_GRAD: blocks z0 .. z0 + nz - 1
 };
 
+template <typename T> constexpr int kblk() { return sizeof(T) == 4 ? 256 : 64; }
+
+// Sums of A over the samples of block z behind the blocks' sums.
+template <typename T>
+__device__ __forceinline__ double* part_bias(const GemmArgs& a) {
+  return (double*)((char*)a.part + (((size_t)a.nz * a.Mr * a.Nc * sizeof(T) + 15) & ~(size_t)15));
+}
+
+// The tile of C at (i0, j0): lane's elements are given by (row, col) pairs.
 template <typename T, int EPI>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a, Geom g) {
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int i, int j, T v) {
+  if (i >= a.Mr || j >= a.Nc) return;
+  T* c = (T*)a.C + i * a.ldc + j;
+  if constexpr (EPI == E_FWD || EPI == E_FWD_LIN) {
+    v += ((const T*)a.bias)[j];
+    if (EPI == E_FWD) v = v > (T)0 ? v : (T)0;
+    *c = v;
+  } else {
+    if constexpr (EPI == E_ADD) v += *c;
+    if (a.act && !(((const T*)a.act)[i * a.ldc + j] > (T)0)) v = (T)0;
+    *c = v;
+  }
+}
+
+// One element of E_GRAD: its block's sum, or (no room for the blocks) the
+// total of all of them.
+template <typename T>
+__device__ __forceinline__ void grad_store(const GemmArgs& a, const Geom& g, int z, int i, int j, T v, double total) {
+  if (i >= a.Mr || j >= a.Nc) return;
+  if (a.part) ((T*)a.part)[((size_t)z * a.Mr + i) * a.Nc + j] = v;
+  else if (mask_at(g, a.mask_kind, i, j)) a.grad[a.grad_off + (long long)i * a.Nc + j] = total;
+}
+__device__ __forceinline__ double grad_before(const GemmArgs& a, const Geom& g, int i, int j) {
+  return !a.part && i < a.Mr && j < a.Nc && mask_at(g, a.mask_kind, i, j)
+             ? a.grad[a.grad_off + (long long)i * a.Nc + j] : 0.0;
+}
+
+// Sum of A's rows i0 + t over the 16 or 32 staged samples (threads t < 64).
+template <typename T, int BK, int LD>
+__device__ __forceinline__ double stage_sum(const T (&As)[BK][LD], int t) {
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < BK; ++k) s += (double)As[k][t];
+  return s;
+}
+
+// Blocks summed in order onto the gradient: weights, then biases.
+template <typename T>
+__global__ __launch_bounds__(256) void grad_reduce_kernel(GemmArgs a, Geom g) {
+  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long long n = (long long)a.Mr * a.Nc;
+  if (e < n) {
+    const int i = (int)(e / a.Nc), j = (int)(e % a.Nc);
+    if (!mask_at(g, a.mask_kind, i, j)) return;
+    double t = a.grad[a.grad_off + e];
+    for (int z = 0; z < a.nz; ++z) t += (double)((const T*)a.part)[z * n + e];
+    a.grad[a.grad_off + e] = t;
+  } else if (e < n + a.Mr) {
+    const int i = (int)(e - n);
+    const double* pb = part_bias<T>(a);
+    double t = a.grad[a.bias_off + i];
+    for (int z = 0; z < a.nz; ++z) t += pb[(long long)z * a.Mr + i];
+    a.grad[a.bias_off + i] = t;
+  }
+}
+
+// FP64: 16 samples or k at a time through LDS, 4x4 elements per thread.
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_f64_kernel(GemmArgs a, Geom g) {
+  typedef double T;
   __shared__ T As[16][65];
   __shared__ T Bs[16][65];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
   const T* A = (const T*)a.A;
   const T* B = (const T*)a.B;
-  T acc[4][4] = {};
-  for (int k0 = 0; k0 < a.K; k0 += 16) {
-    for (int e = threadIdx.x; e < 1024; e += 256) {
-      const int r = e >> 4, kk = e & 15;        // A tile: 64 rows x 16 k
-      const int gi = i0 + r, gk = k0 + kk;
-      As[kk][r] = (gi < a.Mr && gk < a.K) ? A[gi * a.sa0 + gk * a.sa1] : (T)0;
-      const int kb = e >> 6, c = e & 63;        // B tile: 16 k x 64 cols
-      const int gkb = k0 + kb, gj = j0 + c;
-      Bs[kb][c] = (gkb < a.K && gj < a.Nc) ? B[gkb * a.sb0 + gj * a.sb1] : (T)0;
-    }
-    __syncthreads();
+  const int nblk = EPI == E_GRAD ? (a.part ? 1 : a.nz) : 1;
+  double total[4][4], bsum = 0.0;
+  if constexpr (EPI == E_GRAD) {
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      T av[4], bv[4];
+    for (int p = 0; p < 4; ++p)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) { av[q] = As[kk][ty + 16 * q]; bv[q] = Bs[kk][tx + 16 * q]; }
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[p][q] += av[p] * bv[q];
-    }
-    __syncthreads();
+      for (int q = 0; q < 4; ++q) total[p][q] = grad_before(a, g, i0 + ty + 16 * p, j0 + tx + 16 * q);
   }
+  T acc[4][4] = {};
+  const int bz = EPI == E_GRAD && a.part ? (int)blockIdx.z : 0;
+  for (int z = bz; z < bz + nblk; ++z) {
+    const int kb = EPI == E_GRAD ? (a.z0 + z) * kblk<T>() : 0;
+    const int ke = EPI == E_GRAD ? min(a.K, kb + kblk<T>()) : a.K;
+    double bz_sum = 0.0;
+    for (int k0 = kb; k0 < ke; k0 += 16) {
+      for (int e = threadIdx.x; e < 1024; e += 256) {
+        const int r = EPI == E_GRAD ? e & 63 : e >> 4, kk = EPI == E_GRAD ? e >> 6 : e & 15;   // A: 64 rows x 16 k
+        const int gi = i0 + r, gk = k0 + kk;
+        As[kk][r] = (gi < a.Mr && gk < ke) ? (EPI == E_GRAD ? A[gk * a.sa + gi] : A[gi * a.sa + gk]) : 0.0;
+        constexpr bool BK_ = EPI == E_FWD || EPI == E_FWD_LIN;
+        const int kb2 = BK_ ? e & 15 : e >> 6, c = BK_ ? e >> 4 : e & 63;                      // B: 16 k x 64 cols
+        const int gkb = k0 + kb2, gj = j0 + c;
+        Bs[kb2][c] = (gkb < ke && gj < a.Nc) ? (BK_ ? B[gj * a.sb + gkb] : B[gkb * a.sb + gj]) : 0.0;
+      }
+      __syncthreads();
+      if (EPI == E_GRAD && blockIdx.x == 0 && threadIdx.x < 64) bz_sum += stage_sum(As, threadIdx.x);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const int i = i0 + ty + 16 * p;
-    if (i >= a.Mr) continue;
+      for (int kk = 0; kk < 16; ++kk) {
+        T av[4], bv[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = j0 + tx + 16 * q;
-      if (j >= a.Nc) continue;
-      T v = acc[p][q];
-      if constexpr (EPI == E_FWD || EPI == E_FWD_LIN) {
-        v += ((const T*)a.bias)[j];
-        if (EPI == E_FWD) v = v > (T)0 ? v : (T)0;
-        ((T*)a.C)[i * a.ldc + j] = v;
-      } else if constexpr (EPI == E_STORE) {
-        ((T*)a.C)[i * a.ldc + j] = v;
-      } else if constexpr (EPI == E_ADD) {
-        ((T*)a.C)[i * a.ldc + j] += v;
+        for (int q = 0; q < 4; ++q) { av[q] = As[kk][ty + 16 * q]; bv[q] = Bs[kk][tx + 16 * q]; }
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[p][q] += av[p] * bv[q];
+      }
+      __syncthreads();
+    }
+    if constexpr (EPI == E_GRAD) {
+      if (a.part) {
+        if (blockIdx.x == 0 && threadIdx.x < 64 && i0 + (int)threadIdx.x < a.Mr)
+          part_bias<T>(a)[(long long)z * a.Mr + i0 + threadIdx.x] = bz_sum;
       } else {
-        if (mask_at(g, a.mask_kind, i, j)) a.grad[a.grad_off + (long long)i * a.grad_ld + j] += (double)v;
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) { total[p][q] += acc[p][q]; acc[p][q] = 0.0; }
+        if (z == 0 && i0 + (int)threadIdx.x < a.Mr && threadIdx.x < 64) bsum = a.grad[a.bias_off + i0 + threadIdx.x];
+        bsum += bz_sum;
       }
     }
   }
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = i0 + ty + 16 * p, j = j0 + tx + 16 * q;
+      if constexpr (EPI == E_GRAD) grad_store<T>(a, g, bz, i, j, acc[p][q], total[p][q]);
+      else gemm_epilogue<T, EPI>(a, i, j, acc[p][q]);
+    }
+  if (EPI == E_GRAD && !a.part && blockIdx.x == 0 && threadIdx.x < 64 && i0 + (int)threadIdx.x < a.Mr)
+    a.grad[a.bias_off + i0 + threadIdx.x] = bsum;
 }
 
-// The FP32 form on the matrix cores: the same 64x64 tiles and 16-deep k
-// steps through LDS; each of the four waves owns a 32x32 quarter of the tile
-// and accumulates it with v_mfma_f32_32x32x2f32 (lane l supplies A row l % 32
-// and B column l % 32 at k = l / 32; accumulator r of lane l holds row
+// FP32 on the matrix cores: 32 k at a time through LDS, the next 32 already
+// requested; each of the four waves owns a 32x32 quarter of the tile and
+// accumulates it with v_mfma_f32_32x32x2f32 (lane l supplies A row l % 32 and B
+// column l % 32 at k = l / 32; accumulator r of lane l holds row
 // 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of the quarter).
 typedef __attribute__((ext_vector_type(16))) float gemm_f32x16;
+
+// 32 k x 64 lines of a tile, 8 values per thread.  KC: lines are contiguous
+// along k (a thread takes 8 k of one line), else along the lines (8 lines of
+// one k).  Tensors of the flat layout start at any multiple of 4 bytes, which
+// is the alignment that four-float loads need here.
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+template <bool KC>
+struct TileLoad {
+  static constexpr int LD = KC ? 66 : 68;   // LDS row: no bank conflicts for the stores of either form
+  float v[8];
+  __device__ __forceinline__ void load(const float* p, long long ld, int line0, int lines, int k0, int ke) {
+    const int t = threadIdx.x;
+    const int line = line0 + (KC ? t >> 2 : (t & 7) * 8), k = k0 + (KC ? (t & 3) * 8 : t >> 3);
+    const float* q = p + (KC ? (long long)line * ld + k : (long long)k * ld + line);
+    const int n = KC ? (line < lines ? ke - k : 0) : (k < ke ? lines - line : 0);   // values in range, from the first
+    if (n >= 8) {
+      const float4u x = *(const float4u*)q, y = *(const float4u*)(q + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { v[e] = x[e]; v[4 + e] = y[e]; }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = e < n ? q[e] : 0.f;
+    }
+  }
+  __device__ __forceinline__ void store(float (&s)[32][LD]) const {
+    const int t = threadIdx.x;
+    if constexpr (KC) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[(t & 3) * 8 + e][t >> 2] = v[e];
+    } else {
+      *(float4*)&s[t >> 3][(t & 7) * 8] = make_float4(v[0], v[1], v[2], v[3]);
+      *(float4*)&s[t >> 3][(t & 7) * 8 + 4] = make_float4(v[4], v[5], v[6], v[7]);
+    }
+  }
+};
+
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a, Geom g) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
+  constexpr bool AK = EPI != E_GRAD, BKC = EPI == E_FWD || EPI == E_FWD_LIN;
+  __shared__ __align__(16) float As[32][TileLoad<AK>::LD];
+  __shared__ __align__(16) float Bs[32][TileLoad<BKC>::LD];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wy = wave >> 1, wx = wave & 1;
   const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
@@ -325,48 +468,90 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a, Geom g) {
   const float* B = (const float*)a.B;
   gemm_f32x16 acc = {};
   const int li = lane & 31, lk = lane >> 5;
-  for (int k0 = 0; k0 < a.K; k0 += 16) {
-    for (int e = threadIdx.x; e < 1024; e += 256) {
-      const int r = e >> 4, kk = e & 15;        // A tile: 64 rows x 16 k
-      const int gi = i0 + r, gk = k0 + kk;
-      As[kk][r] = (gi < a.Mr && gk < a.K) ? A[gi * a.sa0 + gk * a.sa1] : 0.f;
-      const int kb = e >> 6, c = e & 63;        // B tile: 16 k x 64 cols
-      const int gkb = k0 + kb, gj = j0 + c;
-      Bs[kb][c] = (gkb < a.K && gj < a.Nc) ? B[gkb * a.sb0 + gj * a.sb1] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 2)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[kk + lk][wy * 32 + li], Bs[kk + lk][wx * 32 + li], acc, 0, 0, 0);
-    __syncthreads();
-  }
   const int j = j0 + wx * 32 + li;
-  if (j >= a.Nc) return;
+  auto row = [&](int r) { return i0 + wy * 32 + 8 * (r >> 2) + 4 * lk + (r & 3); };
+  const int nblk = EPI == E_GRAD && !a.part ? a.nz : 1;
+  const int bz = EPI == E_GRAD && a.part ? (int)blockIdx.z : 0;
+  double total[EPI == E_GRAD ? 16 : 1], bsum = 0.0;
+  if constexpr (EPI == E_GRAD) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) total[r] = grad_before(a, g, row(r), j);
+  }
+  const bool sums = EPI == E_GRAD && blockIdx.x == 0 && threadIdx.x < 64;   // this thread sums row i0 + t of A
+  const int bi = i0 + (int)threadIdx.x;
+  for (int z = bz; z < bz + nblk; ++z) {
+    const int kb = EPI == E_GRAD ? (a.z0 + z) * kblk<float>() : 0;
+    const int ke = EPI == E_GRAD ? min(a.K, kb + kblk<float>()) : a.K;
+    double block_sum = 0.0;
+    TileLoad<AK> la;
+    TileLoad<BKC> lb;
+    la.load(A, a.sa, i0, a.Mr, kb, ke);
+    lb.load(B, a.sb, j0, a.Nc, kb, ke);
+    for (int k0 = kb; k0 < ke; k0 += 32) {
+      la.store(As);
+      lb.store(Bs);
+      __syncthreads();
+      if (k0 + 32 < ke) {
+        la.load(A, a.sa, i0, a.Mr, k0 + 32, ke);
+        lb.load(B, a.sb, j0, a.Nc, k0 + 32, ke);
+      }
+      if (sums) block_sum += stage_sum(As, threadIdx.x);
+#pragma unroll
+      for (int kk = 0; kk < 32; kk += 2)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[kk + lk][wy * 32 + li], Bs[kk + lk][wx * 32 + li], acc, 0, 0, 0);
+      __syncthreads();
+    }
+    if constexpr (EPI == E_GRAD) {
+      if (a.part) {
+        if (sums && bi < a.Mr) part_bias<float>(a)[(long long)z * a.Mr + bi] = block_sum;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) total[r] += (double)acc[r];
+        acc = gemm_f32x16{};
+        if (sums && z == 0 && bi < a.Mr) bsum = a.grad[a.bias_off + bi];
+        bsum += block_sum;
+      }
+    }
+  }
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int i = i0 + wy * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
-    if (i >= a.Mr) continue;
-    float v = acc[r];
-    if constexpr (EPI == E_FWD || EPI == E_FWD_LIN) {
-      v += ((const float*)a.bias)[j];
-      if (EPI == E_FWD) v = v > 0.f ? v : 0.f;
-      ((float*)a.C)[i * a.ldc + j] = v;
-    } else if constexpr (EPI == E_STORE) {
-      ((float*)a.C)[i * a.ldc + j] = v;
-    } else if constexpr (EPI == E_ADD) {
-      ((float*)a.C)[i * a.ldc + j] += v;
-    } else {
-      if (mask_at(g, a.mask_kind, i, j)) a.grad[a.grad_off + (long long)i * a.grad_ld + j] += (double)v;
-    }
+    if constexpr (EPI == E_GRAD) grad_store<float>(a, g, bz, row(r), j, acc[r], total[r]);
+    else gemm_epilogue<float, EPI>(a, row(r), j, acc[r]);
   }
+  if (EPI == E_GRAD && !a.part && sums && bi < a.Mr) a.grad[a.bias_off + bi] = bsum;
 }
 
 template <typename T, int EPI>
-static void gemm(const GemmArgs& a, const Geom& g, hipStream_t s) {
+static void gemm(const GemmArgs& a, const Geom& g, hipStream_t s, unsigned blocks = 1) {
   if (a.Mr <= 0 || a.Nc <= 0) return;
-  dim3 grid((unsigned)((a.Nc + 63) / 64), (unsigned)((a.Mr + 63) / 64));
+  dim3 grid((unsigned)((a.Nc + 63) / 64), (unsigned)((a.Mr + 63) / 64), blocks);
   if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((gemm_mfma_kernel<EPI>), grid, dim3(256), 0, s, a, g);
-  else hipLaunchKernelGGL((gemm_kernel<T, EPI>), grid, dim3(256), 0, s, a, g);
+  else hipLaunchKernelGGL((gemm_f64_kernel<EPI>), grid, dim3(256), 0, s, a, g);
+}
+
+// E_GRAD over all blocks of a.K samples: as many blocks at once as `room` bytes
+// at `part` hold the sums of.  A single block needs none.
+template <typename T>
+static void gemm_grad(GemmArgs a, const Geom& g, void* part, size_t room, hipStream_t s) {
+  if (a.Mr <= 0 || a.Nc <= 0) return;
+  const int nz = (a.K + kblk<T>() - 1) / kblk<T>();
+  const size_t per = (size_t)a.Mr * a.Nc * sizeof(T) + (size_t)a.Mr * 8;
+  const int fit = room > 16 ? (int)std::min<size_t>(nz, (room - 16) / per) : 0;
+  if (nz <= 1 || fit < 2) {
+    a.part = nullptr;
+    a.z0 = 0;
+    a.nz = nz;
+    gemm<T, E_GRAD>(a, g, s);
+    return;
+  }
+  a.part = part;
+  for (int z = 0; z < nz; z += fit) {
+    a.z0 = z;
+    a.nz = std::min(fit, nz - z);
+    gemm<T, E_GRAD>(a, g, s, (unsigned)a.nz);
+    const long long n = (long long)a.Mr * a.Nc + a.Mr;
+    hipLaunchKernelGGL(grad_reduce_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a, g);
+  }
 }
 
 // Bit of qubit j of sample i (g.words 64-bit words per sample).
@@ -381,43 +566,6 @@ __global__ void bits_kernel(Geom g, const uint64_t* __restrict__ x, long long S,
   const long long i = e / g.n;
   const int j = (int)(e % g.n);
   s[e] = qubit_bit(g, x, i, j) ? (T)1 : (T)-1;
-}
-
-template <typename T>
-__global__ void relu_mask_kernel(const T* __restrict__ act, T* __restrict__ d, long long count) {
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < count && !(act[e] > (T)0)) d[e] = (T)0;
-}
-
-// grad[off + j] += sum_i D[i * ld + j] in a fixed order (deterministic): a
-// workgroup takes 64 columns; each of its 16 row segments is summed in order
-// in FP64, then the 16 segment sums in order.
-constexpr int kColsumCols = 64, kColsumSegs = 16;
-template <typename T>
-__global__ __launch_bounds__(kColsumCols * kColsumSegs) void colsum_kernel(const T* __restrict__ D, long long S,
-                                                                           int cols, long long ld,
-                                                                           double* __restrict__ grad, long long off) {
-  __shared__ double part[kColsumSegs][kColsumCols];
-  const int c = threadIdx.x % kColsumCols, sg = threadIdx.x / kColsumCols;
-  const int j = blockIdx.x * kColsumCols + c;
-  const long long per = (S + kColsumSegs - 1) / kColsumSegs;
-  const long long i0 = sg * per, i1 = i0 + per < S ? i0 + per : S;
-  double acc = 0.0;
-  if (j < cols)
-    for (long long i = i0; i < i1; ++i) acc += (double)D[i * ld + j];
-  part[sg][c] = acc;
-  __syncthreads();
-  if (sg == 0 && j < cols) {
-    double t = 0.0;
-    for (int q = 0; q < kColsumSegs; ++q) t += part[q][c];
-    grad[off + j] += t;
-  }
-}
-template <typename T>
-static void colsum(const T* D, long long S, int cols, long long ld, double* grad, long long off, hipStream_t s) {
-  if (cols <= 0) return;
-  hipLaunchKernelGGL(colsum_kernel<T>, dim3((unsigned)((cols + kColsumCols - 1) / kColsumCols)),
-                     dim3(kColsumCols * kColsumSegs), 0, s, D, S, cols, ld, grad, off);
 }
 
 // Output seeds for sample i with g_la = 2 (w/W)(Re l - E), g_phi = 2 (w/W) Im l:
@@ -479,40 +627,38 @@ static void mlp_forward(const Geom& g, const T* wm, const T* in0, int k0, long l
     GemmArgs a{};
     a.Mr = (int)S; a.Nc = h; a.K = K;
     a.A = l == 1 ? (const void*)in0 : (const void*)(acts + (long long)(l - 2) * S * h);
-    a.sa0 = K; a.sa1 = 1;
-    a.B = wm + g.poff[wi(l)]; a.sb0 = 1; a.sb1 = K;
+    a.sa = K;
+    a.B = wm + g.poff[wi(l)]; a.sb = K;
     a.C = acts + (long long)(l - 1) * S * h; a.ldc = h;
     a.bias = wm + g.poff[wi(l) + 1];
     gemm<T, E_FWD>(a, g, s);
   }
 }
 
-// Reverse pass through those layers from d(acts[L]) in da: gradients of the
-// weights (masked by mask_of(l)) and biases; da and dz are S x h scratch.
+// Reverse pass through those layers from d(acts[L]), already past the last
+// ReLU, in da: gradients of the weights (masked by mask_of(l)) and biases; da
+// and dz are S x h scratch.
 template <typename T, class WIdx, class MIdx>
 static void mlp_backward(const Geom& g, const T* wm, const T* in0, int k0, long long S, const T* acts, T* da,
-                         T* dz, double* grad, WIdx wi, MIdx mask_of, hipStream_t s) {
+                         T* dz, double* grad, void* part, size_t room, WIdx wi, MIdx mask_of, hipStream_t s) {
   const int h = g.h;
   for (int l = g.L; l >= 1; --l) {
     const int K = l == 1 ? k0 : h;
-    const T* act = acts + (long long)(l - 1) * S * h;
     const T* prev = l == 1 ? in0 : acts + (long long)(l - 2) * S * h;
-    const long long cnt = S * h;
-    hipLaunchKernelGGL(relu_mask_kernel<T>, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, act, da, cnt);
     GemmArgs a{};
     a.Mr = h; a.Nc = K; a.K = (int)S;
-    a.A = da; a.sa0 = 1; a.sa1 = h;
-    a.B = prev; a.sb0 = K; a.sb1 = 1;
-    a.grad = grad; a.grad_off = g.poff[wi(l)]; a.grad_ld = K;
+    a.A = da; a.sa = h;
+    a.B = prev; a.sb = K;
+    a.grad = grad; a.grad_off = g.poff[wi(l)]; a.bias_off = g.poff[wi(l) + 1];
     a.mask_kind = mask_of(l);
-    gemm<T, E_GRAD>(a, g, s);
-    colsum<T>(da, S, h, (long long)h, grad, g.poff[wi(l) + 1], s);
+    gemm_grad<T>(a, g, part, room, s);
     if (l > 1) {
       GemmArgs b{};
       b.Mr = (int)S; b.Nc = K; b.K = h;
-      b.A = da; b.sa0 = h; b.sa1 = 1;
-      b.B = wm + g.poff[wi(l)]; b.sb0 = K; b.sb1 = 1;
+      b.A = da; b.sa = h;
+      b.B = wm + g.poff[wi(l)]; b.sb = K;
       b.C = dz; b.ldc = K;
+      b.act = prev;
       gemm<T, E_STORE>(b, g, s);
       T* t = da; da = dz; dz = t;
     }
@@ -521,7 +667,8 @@ static void mlp_backward(const Geom& g, const T* wm, const T* in0, int k0, long 
 
 template <typename T>
 static void backward_t(const Geom& g, const T* wm, const uint64_t* x, long long S, const double* eloc,
-                       const double* w, const double* energy, T* scratch, double* grad, hipStream_t s) {
+                       const double* w, const double* energy, T* scratch, double* grad, void* part, size_t room,
+                       hipStream_t s) {
   const int n = g.n, h = g.h, L = g.L, ld = n + 4;
   const bool two = g.phase_mode == 1;
   T* sb = scratch;
@@ -548,54 +695,57 @@ static void backward_t(const Geom& g, const T* wm, const uint64_t* x, long long 
     phin = pacts + (long long)(L - 1) * S * h;
   }
   const int hw[2] = {2 * L, poff_phase_head(g)};
-  for (int part = 0; part < 2; ++part) {
+  for (int head = 0; head < 2; ++head) {
     GemmArgs a{};
-    a.Mr = (int)S; a.Nc = part == 0 ? n : 4; a.K = h;
-    a.A = part == 0 ? aL : phin; a.sa0 = h; a.sa1 = 1;
-    a.B = wm + g.poff[hw[part]]; a.sb0 = 1; a.sb1 = h;
-    a.C = hout + (part == 0 ? 0 : n); a.ldc = ld;
-    a.bias = wm + g.poff[hw[part] + 1];
+    a.Mr = (int)S; a.Nc = head == 0 ? n : 4; a.K = h;
+    a.A = head == 0 ? aL : phin; a.sa = h;
+    a.B = wm + g.poff[hw[head]]; a.sb = h;
+    a.C = hout + (head == 0 ? 0 : n); a.ldc = ld;
+    a.bias = wm + g.poff[hw[head] + 1];
     gemm<T, E_FWD_LIN>(a, g, s);
   }
   hipLaunchKernelGGL(seed_kernel<T>, dim3((unsigned)((S + 255) / 256)), dim3(256), 0, s, g, x, S, eloc, w,
                      energy, hout, dh);
   // head gradients
-  for (int part = 0; part < 2; ++part) {
+  for (int head = 0; head < 2; ++head) {
     GemmArgs a{};
-    a.Mr = part == 0 ? n : 4; a.Nc = h; a.K = (int)S;
-    a.A = dh + (part == 0 ? 0 : n); a.sa0 = 1; a.sa1 = ld;
-    a.B = part == 0 ? aL : phin; a.sb0 = h; a.sb1 = 1;
-    a.grad = grad; a.grad_off = g.poff[hw[part]]; a.grad_ld = h;
-    a.mask_kind = part == 0 ? MK_HEAD_O : (two ? MK_NONE : MK_HEAD_P);
-    gemm<T, E_GRAD>(a, g, s);
-    colsum<T>(dh + (part == 0 ? 0 : n), S, a.Mr, (long long)ld, grad, g.poff[hw[part] + 1], s);
+    a.Mr = head == 0 ? n : 4; a.Nc = h; a.K = (int)S;
+    a.A = dh + (head == 0 ? 0 : n); a.sa = ld;
+    a.B = head == 0 ? aL : phin; a.sb = h;
+    a.grad = grad; a.grad_off = g.poff[hw[head]]; a.bias_off = g.poff[hw[head] + 1];
+    a.mask_kind = head == 0 ? MK_HEAD_O : (two ? MK_NONE : MK_HEAD_P);
+    gemm_grad<T>(a, g, part, room, s);
   }
-  // d a_L = d o (M_o W_o) [+ d p (M_p W_p) with the shared trunk]
+  // d a_L = d o (M_o W_o) [+ d p (M_p W_p) with the shared trunk], through the last ReLU
   {
     GemmArgs a{};
     a.Mr = (int)S; a.Nc = h; a.K = n;
-    a.A = dh; a.sa0 = ld; a.sa1 = 1;
-    a.B = wm + g.poff[2 * L]; a.sb0 = h; a.sb1 = 1;
+    a.A = dh; a.sa = ld;
+    a.B = wm + g.poff[2 * L]; a.sb = h;
     a.C = da; a.ldc = h;
+    a.act = two ? aL : nullptr;
     gemm<T, E_STORE>(a, g, s);
     if (!two) {
       a.K = 4;
       a.A = dh + n;
       a.B = wm + g.poff[hw[1]];
+      a.act = aL;
       gemm<T, E_ADD>(a, g, s);
     }
   }
-  mlp_backward<T>(g, wm, sb, n, S, acts, da, dz, grad, trunk_w,
+  mlp_backward<T>(g, wm, sb, n, S, acts, da, dz, grad, part, room, trunk_w,
                   [&](int l) { return l == 1 ? (int)MK_L1 : (int)MK_HID; }, s);
   if (two) {
     // d c_L = d p W_p, then through the phase network's dense layers
     GemmArgs a{};
     a.Mr = (int)S; a.Nc = h; a.K = 4;
-    a.A = dh + n; a.sa0 = ld; a.sa1 = 1;
-    a.B = wm + g.poff[hw[1]]; a.sb0 = h; a.sb1 = 1;
+    a.A = dh + n; a.sa = ld;
+    a.B = wm + g.poff[hw[1]]; a.sb = h;
     a.C = da; a.ldc = h;
+    a.act = phin;
     gemm<T, E_STORE>(a, g, s);
-    mlp_backward<T>(g, wm, pin, n - 2, S, pacts, da, dz, grad, phase_w, [&](int) { return (int)MK_NONE; }, s);
+    mlp_backward<T>(g, wm, pin, n - 2, S, pacts, da, dz, grad, part, room, phase_w, [&](int) { return (int)MK_NONE; },
+                    s);
   }
 }
 
@@ -607,12 +757,12 @@ long long backward_scratch_elems(const Geom& g, long long S) {
 
 void launch_backward(const Geom& g, const void* wm, const uint64_t* x, long long S,
                      const double* eloc, const double* w, const double* energy, void* scratch,
-                     double* grad, hipStream_t s) {
+                     double* grad, void* part, size_t room, hipStream_t s) {
   if (S <= 0) return;
   if (g.prec == P_F64)
-    backward_t<double>(g, (const double*)wm, x, S, eloc, w, energy, (double*)scratch, grad, s);
+    backward_t<double>(g, (const double*)wm, x, S, eloc, w, energy, (double*)scratch, grad, part, room, s);
   else
-    backward_t<float>(g, (const float*)wm, x, S, eloc, w, energy, (float*)scratch, grad, s);
+    backward_t<float>(g, (const float*)wm, x, S, eloc, w, energy, (float*)scratch, grad, part, room, s);
 }
 
 }  // namespace nqs

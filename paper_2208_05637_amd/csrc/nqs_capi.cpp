@@ -1097,9 +1097,13 @@ static void energy_and_grad(nqs_plan* p, const float* params, const uint64_t* x,
   void* wm = at<void>(ws, L.wm);
   launch_pack_masked(p->g, params, wm, s);
   void* scratch = at<void>(ws, L.bscratch);
+  // the local energies are done: their buffers take the gradient's partial sums
+  void* part = at<void>(ws, L.cnt);
+  const size_t room = L.bscratch - L.cnt;
   for (int64_t c0 = 0; c0 < B; c0 += p->Sb) {
     const int64_t Sc = std::min<int64_t>(p->Sb, B - c0);
-    launch_backward(p->g, wm, x + c0 * p->g.words, Sc, el + 2 * c0, w ? w + c0 : nullptr, energy, scratch, grad, s);
+    launch_backward(p->g, wm, x + c0 * p->g.words, Sc, el + 2 * c0, w ? w + c0 : nullptr, energy, scratch, grad, part,
+                    room, s);
   }
 }
 

@@ -123,11 +123,12 @@ void launch_tree_forward(const Geom& g, const TreePlan& t, int ksplit, const voi
 // backward: recompute the sample forward on S samples and accumulate the
 // gradient into grad (f64, flat parameter layout).  scratch holds
 // backward_scratch_elems(g, S) elements of the path's backward type
-// (double for the FP64 path, float otherwise).
+// (double for the FP64 path, float otherwise); part: room bytes for the sums
+// of blocks of samples (any size: with less room fewer blocks run at once).
 long long backward_scratch_elems(const Geom& g, long long S);
 void launch_backward(const Geom& g, const void* wm, const uint64_t* x, long long S,
                      const double* eloc, const double* w, const double* energy, void* scratch,
-                     double* grad, hipStream_t s);
+                     double* grad, void* part, size_t room, hipStream_t s);
 
 // Sampler buffers (kernels_sample.hip); capacity umax entries, children 2 umax.
 struct SampleBufs {
