@@ -323,10 +323,12 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
     rows = c < rows ? c : rows;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && ta.prof_slot) *ta.prof_slot = rows;
-  // Segments: about four per workgroup (their first tiles repeat the upper
-  // levels), 256 to 16384 rows.
-  long long seg = (rows + 4LL * gridDim.x - 1) / (4LL * gridDim.x);
-  seg = seg < 256 ? 256 : (seg > 16384 ? 16384 : (seg + M - 1) / M * M);
+  // Segments repeat the upper levels' first tiles, so there are few: one per
+  // workgroup up to 1,024 rows each, else about four, of at most 16,384 rows.
+  long long seg = (rows + gridDim.x - 1) / gridDim.x;
+  if (seg > 1024) seg = (seg + 3) / 4;
+  seg = seg > 16384 ? 16384 : (seg + M - 1) / M * M;
+  if (seg < M) seg = M;
   const long long nseg = (rows + seg - 1) / seg;
 
   // One tile of c nodes of level j, at nodes half .. of the level's state (rows
@@ -655,6 +657,7 @@ bool plan_levels(const Geom& g, TreePlan& t) {
   constexpr int M = 2 * T::TB;
   const int most = T::SLOTS * kWaves * T::RB / 2;        // own blocks a workgroup can hold
   t.args = TreeArgs{};
+  t.rows = M;
   TreeArgs& a = t.args;
   int ca = 0, ta = 0;
   long long bytes = 0;
@@ -772,7 +775,7 @@ void launch_tree_forward(const Geom& g, const TreePlan& t, int ksplit, const voi
   a.prof_slot = prof_slot;
   a.scratch = (char*)scratch;
   a.ksplit = ksplit;
-  grid = (int)std::min<long long>(grid, (rows_bound + 255) / 256);
+  grid = (int)std::min<long long>(grid, (rows_bound + t.rows - 1) / t.rows);
 #define NQS_TREE(P)                                                     \
   if (g.prec == P) {                                                    \
     if (g.words == 2) launch_w<P, 2>(g, t, a, grid, s);                 \

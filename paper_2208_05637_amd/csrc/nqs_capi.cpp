@@ -242,7 +242,7 @@ static WsLayout layout(const nqs_plan* p, int64_t B) {
   L.tree_grid = 0;
   if (p->tree) {
     // two workgroups per CU, and no more than the chunk has smallest segments
-    L.tree_grid = (int)std::min<int64_t>(2 * std::max(p->ctx->cu_count, 1), (p->EC + 255) / 256);
+    L.tree_grid = (int)std::min<int64_t>(2 * std::max(p->ctx->cu_count, 1), (p->EC + p->tp.rows - 1) / p->tp.rows);
     take((size_t)L.tree_grid * p->tp.args.scratch_wg);
   }
   L.full = o;
@@ -808,7 +808,6 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
     p->packed_phase = align256(p->packed_bytes);
     p->packed_bytes = p->packed_phase + packed_bytes_of(p->gp);
   }
-  p->tree = tree_plan(p->g, p->tp);
   {
     // unmasked weights per configuration (MADE masks) and MFMA work issued
     const int n = g.n, h = g.h;
@@ -849,6 +848,17 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
     const double mult1 = mult > 1.0 ? mult - 1.0 : 1.0;
     p->flops_exec_phase_row = 2.0 * g.TB * g.KSTEP * (mult1 * (double)ph1 + mult * (double)ph);
     p->flops_exec_row = 2.0 * g.TB * g.KSTEP * (mult1 * (double)fr1 + mult * (double)fr) + p->flops_exec_phase_row;
+  }
+  // A walk down the tree takes a handful of tiles one after the other, 60 us and
+  // more however few the rows; row by row they are one wave of tiles over the
+  // CUs.  So a chunk that the row-by-row forward does in about 100 us stays
+  // with it (12 qubits, FP64, 64 units, a chunk of 30,000 entries: 9 us against
+  // 86).  Rates: what the row-by-row kernels reach, per CU.
+  {
+    const double rate = (g.prec == P_F64 ? 60e12 : g.prec == P_F32 ? 130e12 : 1100e12) / 256;
+    const double rows = forward_rows_per_block(g.prec, g.h);
+    const double waves = std::ceil((double)p->EC / (rows * std::max(ctx->cu_count, 1)));
+    p->tree = waves * (8e-6 + rows * p->flops_exec_row / rate) > 100e-6 && tree_plan(p->g, p->tp);
   }
   *out = p;
   return NQS_OK;

@@ -107,6 +107,7 @@ struct TreeArgs {
 struct TreePlan {
   TreeArgs args;
   size_t lds;
+  int rows;   // nodes of a tile
 };
 // Levels of the network's tree; false where it has none (a sampling order the
 // enumeration does not walk depth first, the dense phase network, a network of
