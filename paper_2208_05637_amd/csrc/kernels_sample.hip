@@ -282,17 +282,196 @@ __global__ void sample_finish_kernel(const uint64_t* __restrict__ x, const long 
   ow[i] = (double)cnt[i];
 }
 
+// The step's elimination and compaction in one workgroup, for buffers of up to
+// kFoldEntries entries: the same threshold, quota and order as the kernels
+// above.  Ten launches of a few microseconds each and 40 passes of the
+// bisection over the counts took 130 us a step at 16,384 entries (60 us at
+// 1,000); this takes 28 us (9 us): two to four passes over the counts and one
+// over the children, each bound by the latency of one CU's loads.
+//
+// Threshold: the counts are binned by their magnitude and next five bits (exact
+// below 64), the bin that holds the umax-th largest count is found from the
+// top, and the remaining bits of that bin's counts are binned 11 at a time.
+constexpr int kFoldBins = 2048;
+
+__device__ __forceinline__ int fold_bin(unsigned long long v) {
+  const int e = 63 - __clzll((long long)v);
+  return e < 5 ? (int)v : (e - 4) * 32 + (int)((v >> (e - 5)) & 31);
+}
+
+// From the top, the bin in which the running count reaches `want` (>= 1): bin
+// and the count above it.  Every thread gets both.
+__device__ void fold_find(const unsigned* hist, long long want, long long* sh, int& bin, long long& above) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  // thread t holds bins 2047 - 2t and 2046 - 2t
+  const long long a = hist[kFoldBins - 1 - 2 * t], b = hist[kFoldBins - 2 - 2 * t];
+  long long run = a + b;
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long u = __shfl_up(run, o);
+    if (lane >= o) run += u;
+  }
+  if (lane == 63) sh[w] = run;
+  __syncthreads();
+  for (int k = 0; k < w; ++k) run += sh[k];
+  const long long before = run - a - b;
+  if (before < want && run >= want) {
+    const bool first = before + a >= want;
+    sh[16] = kFoldBins - 1 - 2 * t - (first ? 0 : 1);
+    sh[17] = first ? before : before + a;
+  }
+  __syncthreads();
+  bin = (int)sh[16];
+  above = sh[17];
+  __syncthreads();
+}
+
+template <int W>
+__global__ __launch_bounds__(kSelThreads) void sample_fold_kernel(const uint64_t* __restrict__ kx,
+                                                                 const long long* __restrict__ kc, long long umax,
+                                                                 uint64_t* __restrict__ x, long long* __restrict__ cnt,
+                                                                 const int* __restrict__ anc_in,
+                                                                 int* __restrict__ anc_out, long long* d_u) {
+  __shared__ unsigned hist[kFoldBins];
+  __shared__ long long sh[18];
+  __shared__ int ngt[kSelThreads / 64], neq[kSelThreads / 64];
+  static_assert(kFoldBins == 2 * kSelThreads, "two bins per thread");
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int U = (int)*d_u, nk = 2 * U;
+  // each wave takes a run of children, 64 at a time in order
+  const int per = ((nk + kSelThreads - 1) / kSelThreads) * 64;
+  const int i0 = wv * per, i1 = i0 + per < nk ? i0 + per : nk;
+  constexpr int B = 8;                           // groups of 64 in flight: the loads' latency is most of a pass
+  auto load = [&](long long (&v)[B], int j) {
+#pragma unroll
+    for (int k = 0; k < B; ++k) v[k] = j + 64 * k < i1 ? kc[min(j + 64 * k + lane, nk - 1)] : 0;
+#pragma unroll
+    for (int k = 0; k < B; ++k) v[k] = j + 64 * k + lane < i1 ? v[k] : 0;
+  };
+  // fn(count) for the wave's children in order, 64 lanes at once; past the run's end the count is 0
+  auto each = [&](auto fn) {
+    for (int j = i0; j < i1; j += 64 * B) {
+      long long v[B];
+      load(v, j);
+#pragma unroll
+      for (int k = 0; k < B; ++k)
+        if (j + 64 * k < i1) fn(v[k]);
+    }
+  };
+  auto clear = [&]() {
+    hist[tid] = 0;
+    hist[tid + kSelThreads] = 0;
+    __syncthreads();
+  };
+  clear();
+  each([&](long long v) {
+    if (v > 0) atomicAdd(&hist[fold_bin((unsigned long long)v)], 1u);
+  });
+  __syncthreads();
+  long long nz = 0;
+  {
+    long long v = (long long)hist[tid] + hist[tid + kSelThreads];
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    if (lane == 0) sh[wv] = v;
+    __syncthreads();
+    for (int k = 0; k < kSelThreads / 64; ++k) nz += sh[k];
+    __syncthreads();
+  }
+  long long tau = 0, quota = 0;
+  if (nz > umax) {
+    int bin;
+    long long above, need = umax;
+    fold_find(hist, need, sh, bin, above);
+    need -= above;
+    // the bin's counts: [lo, lo + 2^shift)
+    int shift = bin < 32 ? 0 : bin / 32 - 1;
+    unsigned long long lo = bin < 32 ? (unsigned long long)bin : (unsigned long long)(32 + bin % 32) << shift;
+    while (shift > 0) {
+      const int r = shift < 11 ? shift : 11;
+      clear();
+      each([&](long long v) {
+        const unsigned long long d = (unsigned long long)v - lo;
+        if ((d >> shift) == 0) atomicAdd(&hist[d >> (shift - r)], 1u);
+      });
+      __syncthreads();
+      fold_find(hist, need, sh, bin, above);
+      need -= above;
+      shift -= r;
+      lo += (unsigned long long)bin << shift;
+    }
+    tau = (long long)lo;
+    quota = need;
+  }
+  int gt = 0, eq = 0;
+  each([&](long long v) {
+    gt += __popcll(__ballot(v > tau));
+    eq += __popcll(__ballot(tau > 0 && v == tau));
+  });
+  if (lane == 0) {
+    ngt[wv] = gt;
+    neq[wv] = eq;
+  }
+  __syncthreads();
+  int before_gt = 0, rank = 0;
+  for (int k = 0; k < wv; ++k) {
+    before_gt += ngt[k];
+    rank += neq[k];
+  }
+  const int q = (int)quota;
+  int dst = before_gt + (rank < q ? rank : q);
+  const unsigned long long below = (1ull << lane) - 1;
+  for (int j = i0; j < i1; j += 64 * B) {
+    long long v[B];
+    uint64_t xv[B][W];
+    int an[B];
+    load(v, j);
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+      if (j + 64 * k >= i1) break;
+      const int i = min(j + 64 * k + lane, nk - 1), parent = i < U ? i : i - U;
+#pragma unroll
+      for (int w = 0; w < W; ++w) xv[k][w] = kx[(long long)i * W + w];
+      an[k] = anc_in ? anc_in[parent] : parent;
+    }
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+      if (j + 64 * k >= i1) break;
+      const bool tie = tau > 0 && v[k] == tau;
+      const unsigned long long be = __ballot(tie);
+      const bool keep = v[k] > tau || (tie && rank + __popcll(be & below) < q);
+      const unsigned long long bk = __ballot(keep);
+      if (keep) {
+        const int d = dst + __popcll(bk & below);
+#pragma unroll
+        for (int w = 0; w < W; ++w) x[(long long)d * W + w] = xv[k][w];
+        cnt[d] = v[k];
+        if (anc_out) anc_out[d] = an[k];
+      }
+      rank += __popcll(be);
+      dst += __popcll(bk);
+    }
+  }
+  if (tid == 0) *d_u = nz < umax ? nz : umax;
+}
+
 static unsigned blocks_for(long long n, int t) { return (unsigned)((n + t - 1) / t); }
 
 void launch_sample_init(uint64_t* x, int words, long long* cnt, long long n_draws, long long* d_u, hipStream_t s) {
   hipLaunchKernelGGL(sample_init_kernel, dim3(1), dim3(1), 0, s, x, words, cnt, n_draws, d_u);
 }
 
-void launch_sample_step(const SampleBufs& b, long long umax, int t, int q, uint64_t seed, hipStream_t s) {
+void launch_sample_step(const SampleBufs& b, long long umax, int t, int q, uint64_t seed, const int* anc_in,
+                        int* anc_out, hipStream_t s) {
   const long long n2 = 2 * umax;
   auto split = b.words == 2 ? sample_split_kernel<2> : sample_split_kernel<1>;
-  hipLaunchKernelGGL(split, dim3(blocks_for(umax, 256)), dim3(256), 0, s, b.x, b.cnt,
+  // one wave per workgroup: lanes of a wave differ in how long they draw, and
+  // more workgroups spread over more CUs (17 -> 15 us at 16,384 entries)
+  hipLaunchKernelGGL(split, dim3(blocks_for(umax, 64)), dim3(64), 0, s, b.x, b.cnt,
                      (const double2*)b.cond, b.d_u, umax, t, q, seed, b.kx, b.kc, b.d_nk);
+  if (umax <= kFoldEntries) {
+    auto fold = b.words == 2 ? sample_fold_kernel<2> : sample_fold_kernel<1>;
+    hipLaunchKernelGGL(fold, dim3(1), dim3(kSelThreads), 0, s, b.kx, b.kc, umax, b.x, b.cnt, anc_in, anc_out, b.d_u);
+    return;
+  }
   hipLaunchKernelGGL(sample_select_kernel, dim3(1), dim3(kSelThreads), 0, s, b.kc, b.d_nk, umax, b.sel);
   hipLaunchKernelGGL(sample_tie_flags, dim3(blocks_for(n2, 256)), dim3(256), 0, s, b.kc, b.d_nk, b.sel, n2, b.eq);
   launch_scan(b.eq, n2, b.eqoff, b.stmp, s);

@@ -94,6 +94,10 @@ struct Weights {
   int plane;   // bytes to the low plane
   int voff;    // lane * 16
 };
+__device__ __forceinline__ Weights weights(const Geom& g, const void* packed) {
+  return Weights{__builtin_amdgcn_make_buffer_rsrc((void*)packed, (short)0, (int)g.bias_byte, 0x00020000),
+                 (int)(g.nfrag * 1024), 0};
+}
 template <int P>
 __device__ __forceinline__ void wload(const Weights& b, int soff, uint4 (&w)[Kind<P>::PLW]) {
   w[0] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b.rsrc, b.voff, soff, 0));
@@ -229,33 +233,34 @@ __device__ __forceinline__ void store_act(char* act, const typename Kind<P>::Acc
 
 // A block of TB pre-activations x TB nodes in a level's state: unit-major in
 // groups of four (FP64: single units), nodes adjacent, so a wave's loads and
-// stores of neighbouring nodes are contiguous.  unit0: first unit of the block.
+// stores of neighbouring nodes are contiguous.  nodes: places per unit, unit0:
+// first unit of the block.
 template <int P>
-__device__ __forceinline__ void state_load(typename Kind<P>::Acc& acc, const char* st, int unit0, int node, int lane) {
-  constexpr int M = 4 * Kind<P>::TB;                           // nodes of a state: two tiles
+__device__ __forceinline__ void state_load(typename Kind<P>::Acc& acc, const char* st, unsigned nodes, int unit0,
+                                           int node, int lane) {
   const int g = lane / Kind<P>::TB;
   if constexpr (P == P_F64) {
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[rr] = *(const double*)(st + (unsigned)((unit0 + g + 4 * rr) * M + node) * 8u);
+    for (int rr = 0; rr < 4; ++rr) acc[rr] = *(const double*)(st + ((unit0 + g + 4 * rr) * nodes + node) * 8u);
   } else {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const float4 v = *(const float4*)(st + (unsigned)((unit0 / 4 + 2 * q + g) * M + node) * 16u);
+      const float4 v = *(const float4*)(st + ((unit0 / 4 + 2 * q + g) * nodes + node) * 16u);
       acc[4 * q] = v.x; acc[4 * q + 1] = v.y; acc[4 * q + 2] = v.z; acc[4 * q + 3] = v.w;
     }
   }
 }
 template <int P>
-__device__ __forceinline__ void state_store(const typename Kind<P>::Acc& acc, char* st, int unit0, int node, int lane) {
-  constexpr int M = 4 * Kind<P>::TB;                           // nodes of a state: two tiles
+__device__ __forceinline__ void state_store(const typename Kind<P>::Acc& acc, char* st, unsigned nodes, int unit0,
+                                            int node, int lane) {
   const int g = lane / Kind<P>::TB;
   if constexpr (P == P_F64) {
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) *(double*)(st + (unsigned)((unit0 + g + 4 * rr) * M + node) * 8u) = acc[rr];
+    for (int rr = 0; rr < 4; ++rr) *(double*)(st + ((unit0 + g + 4 * rr) * nodes + node) * 8u) = acc[rr];
   } else {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      *(float4*)(st + (unsigned)((unit0 / 4 + 2 * q + g) * M + node) * 16u) =
+      *(float4*)(st + ((unit0 / 4 + 2 * q + g) * nodes + node) * 16u) =
           make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
   }
 }
@@ -289,33 +294,249 @@ __host__ __device__ inline long long state_units(const Geom& g, int cb) {
   return ((long long)(g.L - 1) * (g.NB - cb) + 2LL * g.NHB) * Kind<P>::TB;
 }
 
+// LDS of a tile of M nodes.
+template <int P, int W>
+struct TileLds {
+  using S = typename Kind<P>::S;
+  static constexpr int M = 2 * Kind<P>::TB;
+  char* act;           // activations of the level's own units, by k fragment and row block
+  int plane;           // bytes to their low plane
+  S* stage;            // [M][stage_ld] head outputs
+  int stage_ld;
+  S* blds;             // bias of the layer being finished
+  S* hbl;              // bias of the head rows being finished
+  uint64_t* ylds;      // the nodes' prefixes, in sampling order
+  int* pidx;           // the nodes' parents: places in the parents' state
+  __device__ TileLds(void* smem, int own_max, int ld) {
+    act = (char*)smem;
+    plane = own_max * (Kind<P>::TB / Kind<P>::KSTEP) * 2 * 1024;
+    stage = (S*)(act + Kind<P>::PL * plane);
+    stage_ld = ld;
+    blds = stage + M * ld;
+    hbl = blds + own_max * Kind<P>::TB;
+    ylds = (uint64_t*)(hbl + ld + 1);                          // ld is odd
+    pidx = (int*)(ylds + M * W);
+  }
+  __device__ __forceinline__ void put_prefix(int at, const uint64_t* x, int n) const {   // reverse sampling order
+    if constexpr (W == 1) {
+      ylds[at] = __builtin_bitreverse64(x[0]) >> (64 - n);
+    } else {
+      const uint64_t r0 = __builtin_bitreverse64(x[1]), r1 = __builtin_bitreverse64(x[0]);
+      const int sh = 128 - n;
+      ylds[2 * at] = sh == 0 ? r0 : ((r0 >> sh) | (r1 << (64 - sh)));
+      ylds[2 * at + 1] = r1 >> sh;
+    }
+  }
+};
+
+// What a tile evaluates: units of blocks [ca, eb) given the parents' state of
+// the units before ca (pst, pn places per unit), their head products, and with
+// out the chains of blocks [cb, NB) over blocks [ca, cb) and of the head into
+// the state st (sn places, this tile's from place).  Head rows [r0, r1) end up
+// in the stage, without bias.
+struct TileJob {
+  int ca, cb, eb, r0, r1;
+  bool out;
+  const char* pst;
+  unsigned pn;
+  char* st;
+  unsigned sn;
+  int place;
+};
+
+template <int P, int W>
+__device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W>& t, Weights wb,
+                                           const typename Kind<P>::S* biases, int ksplit, int wv, const TileJob& jb) {
+  using T = Kind<P>;
+  using Acc = typename T::Acc;
+  using S = typename T::S;
+  constexpr int TB = T::TB, KB = TB / T::KSTEP, PL = T::PL, RB = T::RB, SLOTS = T::SLOTS;
+  const int tid = thread_index(), lane = tid & 63, col = lane % TB;
+  wb.voff = lane * 16;
+  const int L = g.L, NB = g.NB, ca = jb.ca, cb = jb.cb, eb = jb.eb;
+  const int ka = ca * KB, own = eb - ca;
+  const int node0 = ca > 0 ? t.pidx[col] : 0, node1 = ca > 0 ? t.pidx[TB + col] : 0;
+  const int pun = (NB - ca) * TB, sun = (NB - cb) * TB;        // units per layer in the parents' state and in this one
+  char* act = t.act;
+  auto lds_act = [&](int mb, int ks, uint4 (&f)[PL]) {
+    const char* a = act + (((ks - ka) * 2 + mb) * 64 + lane) * 16;
+    f[0] = *(const uint4*)a;
+    if constexpr (PL == 2) f[1] = *(const uint4*)(a + t.plane);
+  };
+  // the chain of block b, row blocks mb .., in layer l up to this level's first unit
+  auto parent = [&](Acc (&acc)[RB], int l, int b, int mb) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      acc[i] = Acc{};
+      if (ca > 0)
+        state_load<P>(acc[i], jb.pst, jb.pn, (l - 2) * pun + (b - ca) * TB, (mb + i) ? node1 : node0, lane);
+    }
+  };
+  // The own blocks' tiles are dealt out largest extent first, in a snake over
+  // the waves: waves w and w + 4 share a SIMD, which then gets equal work;
+  // the second workgroup of a CU starts from the other end.
+  const int wd = blockIdx.x >= gridDim.x / 2 ? wv ^ 3 : wv;
+  auto own_block = [&](int s, int& mb) {
+    const int r = (s & 1) ? kWaves * (s + 1) - 1 - wd : kWaves * s + (wd < 4 ? wd : 11 - wd);
+    mb = RB == 2 ? 0 : r & 1;
+    return eb - 1 - r * RB / 2;
+  };
+
+  if (tid < jb.r1 - jb.r0) t.hbl[tid] = biases[(long long)L * g.h + jb.r0 + tid];
+  // the input fragments, in LDS for layer 1
+  if (own > 0) {
+    const int kin = g.ks1[eb - 1];
+    for (int it = wv; it < 2 * kin; it += kWaves)
+      *(uint4*)(act + (it * 64 + lane) * 16) = input_frag<P, W>(t.ylds, it & 1, it >> 1, lane);
+  }
+  lds_barrier();
+  for (int l = 1; own > 0 && l <= L; ++l) {
+    const int lbase = (int)(g.frag_h + (long long)(l - 2) * g.offh[NB]);
+    const S breg = tid < own * TB ? biases[(long long)(l - 1) * g.h + ca * TB + tid] : S(0);
+    Acc acc[SLOTS][RB];
+    if (l == 1) {
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) {
+        int mb;
+        const int b = own_block(s, mb);
+#pragma unroll
+        for (int i = 0; i < RB; ++i) acc[s][i] = Acc{};
+        if (b >= ca)
+          strip<P, true>(acc[s], wb, g.off1[b] * 1024, mb, 0, g.ks1[b], [&](int rb, int ks, uint4 (&f)[PL]) {
+            f[0] = *(const uint4*)(act + ((ks * 2 + rb) * 64 + lane) * 16);
+          });
+      }
+    } else {
+      // later units' chains over these units, into the state
+      if (jb.out) {
+        for (int it = wv; it < (NB - cb) * 2 / RB; it += kWaves) {
+          const int b = cb + it * RB / 2, mb = RB == 2 ? 0 : it & 1;
+          parent(acc[0], l, b, mb);
+          strip<P, false>(acc[0], wb, (lbase + g.offh[b]) * 1024, mb, ka, cb * KB, lds_act);
+#pragma unroll
+          for (int i = 0; i < RB; ++i)
+            state_store<P>(acc[0][i], jb.st, jb.sn, (l - 2) * sun + (b - cb) * TB, jb.place + (mb + i) * TB + col, lane);
+        }
+      }
+      // the own units
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) {
+        int mb;
+        const int b = own_block(s, mb);
+        if (b >= ca) {
+          parent(acc[s], l, b, mb);
+          strip<P, false>(acc[s], wb, (lbase + g.offh[b]) * 1024, mb, ka, min(g.ksh[b], eb * KB), lds_act);
+        }
+      }
+    }
+    if (tid < own * TB) t.blds[tid] = breg;
+    lds_barrier();
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      int mb;
+      const int b = own_block(s, mb);
+      if (b >= ca) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) store_act<P>(act, acc[s][i], t.blds, b - ca, mb + i, lane, t.plane);
+      }
+    }
+    lds_barrier();
+  }
+
+  // head: items of one head block and one row block
+  const int hun = (L - 1) * sun, phun = (L - 1) * pun;
+  for (int item = wv; item < 2 * g.NHB; item += kWaves) {
+    const int nb = item >> 1, mb = item & 1;
+    if (!jb.out && (TB * (nb + 1) <= jb.r0 || TB * nb >= jb.r1)) continue;   // no row wanted
+    const int kso = g.kso[nb];
+    const int chunk = (((kso + ksplit - 1) / ksplit) + 7) & ~7;
+    const int kstop = min(kso, (jb.out ? cb : eb) * KB);
+    const int node = mb ? node1 : node0;
+    Acc v{}, part{};                                           // finished slices, the slice in progress
+    if (ca > 0) {
+      state_load<P>(v, jb.pst, jb.pn, phun + nb * TB, node, lane);
+      state_load<P>(part, jb.pst, jb.pn, phun + (g.NHB + nb) * TB, node, lane);
+    }
+    const int base = (int)(g.frag_head + g.offo[nb]) * 1024;
+    // fragments of up to eight steps requested back to back, then consumed in order
+    constexpr int D = 8 / T::PLW;
+    for (int k = ka; k < kstop;) {
+      const int ke = min(min(kstop, (k / chunk + 1) * chunk), k + D);
+      uint4 w[D][T::PLW];
+#pragma unroll
+      for (int d = 0; d < D; ++d) wload<P>(wb, base + min(k + d, ke - 1) * 1024, w[d]);
+      uint4 f[2][PL];
+      lds_act(mb, k, f[0]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int d = 0; d < D; ++d)
+        if (k + d < ke) {
+          lds_act(mb, min(k + d + 1, ke - 1), f[(d + 1) & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+          mma<P, false>(part, w[d], f[d & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      k = ke;
+      if (ke == kso || ke % chunk == 0) {                      // a slice is finished
+        v += part;
+        part = Acc{};
+      }
+    }
+    if (jb.out) {
+      state_store<P>(v, jb.st, jb.sn, hun + nb * TB, jb.place + mb * TB + col, lane);
+      state_store<P>(part, jb.st, jb.sn, hun + (g.NHB + nb) * TB, jb.place + mb * TB + col, lane);
+    }
+    v += part;
+    const int m = mb * TB + col, gq = lane / TB;
+    constexpr int NR = P == P_F64 ? 4 : 16;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int q = nb * TB + (P == P_F64 ? gq + 4 * r : 8 * (r >> 2) + 4 * gq + (r & 3));
+      if (q >= jb.r0 && q < jb.r1) t.stage[m * t.stage_ld + q - jb.r0] = v[r];
+    }
+  }
+  lds_barrier();
+}
+
+// Spin of the qubit at position t.
+__device__ __forceinline__ int spin_at(const Geom& g, int t) {
+  return (int)(((t < 64 ? g.spin_pos[1] : g.spin_pos_hi[1]) >> (t & 63)) & 1ull);
+}
+// Eq. modifier at position t of spin sp: ones among the earlier positions of
+// that spin and its later positions force the value to 0 (f0) or 1 (f1).
+template <int W>
+__device__ __forceinline__ void forced(const Geom& g, uint64_t y, uint64_t yh, int t, int sp, bool& f0, bool& f1) {
+  const uint64_t m0 = sp ? g.spin_pos[1] : g.spin_pos[0];
+  const uint64_t low0 = t >= 64 ? ~0ull : (1ull << t) - 1;
+  int before = __popcll(y & m0 & low0), rem = __popcll(m0 & ~low0);
+  if constexpr (W == 2) {
+    const uint64_t m1 = sp ? g.spin_pos_hi[1] : g.spin_pos_hi[0];
+    const uint64_t low1 = t <= 64 ? 0ull : (1ull << (t - 64)) - 1;
+    before += __popcll(yh & m1 & low1);
+    rem += __popcll(m1 & ~low1);
+  }
+  rem -= 1;                                                    // position t itself
+  const int ns = sp ? g.n_dn : g.n_up;
+  f0 = before >= ns;
+  f1 = before + rem < ns;
+}
+
 }  // namespace
 
 template <int P, int W>
 __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta) {
-  using T = Kind<P>;
-  using Acc = typename T::Acc;
-  using S = typename T::S;
-  constexpr int TB = T::TB, M = 2 * TB, KB = TB / T::KSTEP, PL = T::PL, RB = T::RB, SLOTS = T::SLOTS;
+  using S = typename Kind<P>::S;
+  constexpr int M = 2 * Kind<P>::TB;
   extern __shared__ uint4 smem[];
-  char* act = (char*)smem;
-  const int plane = ta.own_max * KB * 2 * 1024;
-  S* stage = (S*)(act + PL * plane);                           // [M][stage_ld] head outputs
-  S* blds = stage + M * ta.stage_ld;                           // bias of the layer being finished
-  S* hbl = blds + ta.own_max * TB;                             // bias of the head rows being finished
-  uint64_t* ylds = (uint64_t*)(hbl + ta.stage_ld + 1);         // the tile's prefixes, in sampling order
-  int* pidx = (int*)(ylds + M * W);                            // their parents among the level above
-  int* cur = pidx + M, *pb = cur + 4, *tiles = cur + 8;        // the walk's cursors, per level
+  const TileLds<P, W> t(smem, ta.own_max, ta.stage_ld);
+  int* cur = t.pidx + M, *pb = cur + 4, *tiles = cur + 8;      // the walk's cursors, per level
   int* nxt = cur + 12, *wcnt = cur + 16;                       // first row past the tile; wave counts
 
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = g.n, L = g.L, NB = g.NB;
+  const int n = g.n;
   const S* biases = (const S*)((const char*)ta.packed + g.bias_byte);
-  Weights wb;
-  wb.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)ta.packed, (short)0, (int)g.bias_byte, 0x00020000);
-  wb.plane = (int)(g.nfrag * 1024);
+  const Weights wb = weights(g, ta.packed);
   char* scratch = ta.scratch + (long long)blockIdx.x * ta.scratch_wg;
-  const int nho = g.net_kind == 1 ? n : n + 4;                 // head rows in use
 
   long long rows = ta.bound;
   if (ta.d_count) {
@@ -334,192 +555,35 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
   // One tile of c nodes of level j, at nodes half .. of the level's state (rows
   // row0 .. for the last level).
   auto tile = [&](int j, int c, int half, long long row0) {
-    const int tid = thread_index(), lane = tid & 63, col = lane % TB;
-    wb.voff = lane * 16;
     const TreeLevel& lv = ta.lev[j];
     const bool leaf = j == ta.nlev - 1;
-    const int ca = lv.ca, cb = lv.cb, eb = lv.eb;
-    const int ka = ca * KB;
-    const int own = eb - ca;
     const char* pst = j > 0 ? scratch + ta.lev[j - 1].st : nullptr;
     char* st = scratch + lv.st;
-    const int node0 = j > 0 ? pidx[col] : 0, node1 = j > 0 ? pidx[TB + col] : 0;
-    const int pun = (NB - ca) * TB, sun = (NB - cb) * TB;      // units per layer in the parent's state and in this one
-    const int t1 = leaf ? nho : lv.tb;                         // head rows finished here: [ta, t1)
-    auto lds_act = [&](int mb, int ks, uint4 (&f)[PL]) {
-      const char* a = act + (((ks - ka) * 2 + mb) * 64 + lane) * 16;
-      f[0] = *(const uint4*)a;
-      if constexpr (PL == 2) f[1] = *(const uint4*)(a + plane);
-    };
-    // the chain of block b, row blocks mb .., in layer l up to this level's first unit
-    auto parent = [&](Acc (&acc)[RB], int l, int b, int mb) {
-#pragma unroll
-      for (int i = 0; i < RB; ++i) {
-        acc[i] = Acc{};
-        if (ca > 0) state_load<P>(acc[i], pst, (l - 2) * pun + (b - ca) * TB, (mb + i) ? node1 : node0, lane);
-      }
-    };
-    // The own blocks' tiles are dealt out largest extent first, in a snake over
-    // the waves: waves w and w + 4 share a SIMD, which then gets equal work;
-    // the second workgroup of a CU starts from the other end.
-    const int wd = blockIdx.x >= gridDim.x / 2 ? wv ^ 3 : wv;
-    auto own_block = [&](int s, int& mb) {
-      const int r = (s & 1) ? kWaves * (s + 1) - 1 - wd : kWaves * s + (wd < 4 ? wd : 11 - wd);
-      mb = RB == 2 ? 0 : r & 1;
-      return eb - 1 - r * RB / 2;
-    };
-
-    // the level's input fragments, in LDS for layer 1
-    const int kin = g.ks1[eb - 1];
-    for (int it = wv; it < 2 * kin; it += kWaves) {
-      *(uint4*)(act + (it * 64 + lane) * 16) = input_frag<P, W>(ylds, it & 1, it >> 1, lane);
-    }
-    if (tid < t1 - lv.ta) hbl[tid] = biases[(long long)L * g.h + lv.ta + tid];
-
-    lds_barrier();
-    for (int l = 1; l <= L; ++l) {
-      const int lbase = (int)(g.frag_h + (long long)(l - 2) * g.offh[NB]);
-      const S breg = tid < own * TB ? biases[(long long)(l - 1) * g.h + ca * TB + tid] : S(0);
-      Acc acc[SLOTS][RB];
-      if (l == 1) {
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-          int mb;
-          const int b = own_block(s, mb);
-#pragma unroll
-          for (int i = 0; i < RB; ++i) acc[s][i] = Acc{};
-          if (b >= ca)
-            strip<P, true>(acc[s], wb, g.off1[b] * 1024, mb, 0, g.ks1[b], [&](int rb, int ks, uint4 (&f)[PL]) {
-              f[0] = *(const uint4*)(act + ((ks * 2 + rb) * 64 + lane) * 16);
-            });
-        }
-      } else {
-        // later units' chains over this level's units, into the state
-        if (!leaf) {
-          for (int it = wv; it < (NB - cb) * 2 / RB; it += kWaves) {
-            const int b = cb + it * RB / 2, mb = RB == 2 ? 0 : it & 1;
-            parent(acc[0], l, b, mb);
-            strip<P, false>(acc[0], wb, (lbase + g.offh[b]) * 1024, mb, ka, cb * KB, lds_act);
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-              state_store<P>(acc[0][i], st, (l - 2) * sun + (b - cb) * TB, half + (mb + i) * TB + col, lane);
-          }
-        }
-        // the level's own units
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-          int mb;
-          const int b = own_block(s, mb);
-          if (b >= ca) {
-            parent(acc[s], l, b, mb);
-            strip<P, false>(acc[s], wb, (lbase + g.offh[b]) * 1024, mb, ka, min(g.ksh[b], eb * KB), lds_act);
-          }
-        }
-      }
-      if (tid < own * TB) blds[tid] = breg;
-      lds_barrier();
-#pragma unroll
-      for (int s = 0; s < SLOTS; ++s) {
-        int mb;
-        const int b = own_block(s, mb);
-        if (b >= ca) {
-#pragma unroll
-          for (int i = 0; i < RB; ++i) store_act<P>(act, acc[s][i], blds, b - ca, mb + i, lane, plane);
-        }
-      }
-      lds_barrier();
-    }
-
-    // ---------------------------------------------------------------- head
-    const int hun = (L - 1) * sun, phun = (L - 1) * pun;
-    for (int item = wv; item < 2 * g.NHB; item += kWaves) {
-      const int nb = item >> 1, mb = item & 1;
-      if (leaf && (TB * (nb + 1) <= lv.ta || TB * nb >= nho)) continue;   // complete above, or padding
-      const int kso = g.kso[nb];
-      const int chunk = (((kso + ta.ksplit - 1) / ta.ksplit) + 7) & ~7;
-      const int kstop = leaf ? kso : min(kso, cb * KB);
-      const int node = mb ? node1 : node0;
-      Acc v{}, part{};                                         // finished slices, the slice in progress
-      if (ca > 0) {
-        state_load<P>(v, pst, phun + nb * TB, node, lane);
-        state_load<P>(part, pst, phun + (g.NHB + nb) * TB, node, lane);
-      }
-      const int base = (int)(g.frag_head + g.offo[nb]) * 1024;
-      // fragments of up to eight steps requested back to back, then consumed in order
-      constexpr int D = 8 / T::PLW;
-      for (int k = ka; k < kstop;) {
-        const int ke = min(min(kstop, (k / chunk + 1) * chunk), k + D);
-        uint4 w[D][T::PLW];
-#pragma unroll
-        for (int d = 0; d < D; ++d) wload<P>(wb, base + min(k + d, ke - 1) * 1024, w[d]);
-        uint4 f[2][PL];
-        lds_act(mb, k, f[0]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-          if (k + d < ke) {
-            lds_act(mb, min(k + d + 1, ke - 1), f[(d + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-            mma<P, false>(part, w[d], f[d & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        k = ke;
-        if (ke == kso || ke % chunk == 0) {                    // a slice is finished
-          v += part;
-          part = Acc{};
-        }
-      }
-      if (!leaf) {
-        state_store<P>(v, st, hun + nb * TB, half + mb * TB + col, lane);
-        state_store<P>(part, st, hun + (g.NHB + nb) * TB, half + mb * TB + col, lane);
-      }
-      v += part;
-      const int m = mb * TB + col, gq = lane / TB;
-      constexpr int NR = P == P_F64 ? 4 : 16;
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int t = nb * TB + (P == P_F64 ? gq + 4 * r : 8 * (r >> 2) + 4 * gq + (r & 3));
-        if (t >= lv.ta && t < t1) stage[m * ta.stage_ld + t - lv.ta] = v[r];
-      }
-    }
-    lds_barrier();
+    tile_units<P, W>(g, t, wb, biases, ta.ksplit, wv,
+                     TileJob{lv.ca, lv.cb, lv.eb, lv.ta, leaf ? (g.net_kind == 1 ? n : n + 4) : lv.tb, !leaf, pst,
+                             2 * M, st, 2 * M, half});
 
     // ------------------------------------------------- log-sigmoids, phase
     constexpr int TPR = kThreads / M;
-    const int tid2 = thread_index();
-    const int m = tid2 / TPR, sub = tid2 % TPR;
+    const int tid = thread_index();
+    const int m = tid / TPR, sub = tid % TPR;
     double2 up = make_double2(0.0, 0.0);                       // what the parent has summed
-    if (sub == 0 && j > 0) up = ((const double2*)(pst + state_units<P>(g, ca) * (2 * M) * (long long)sizeof(S)))[pidx[m]];
-    const uint64_t y = ylds[m * W], yh = W == 2 ? ylds[m * W + 1] : 0ull;
-    auto bit = [&](int t) -> int { return (int)(((t < 64 ? y : yh) >> (t & 63)) & 1ull); };
-    auto out = [&](int t) { return stage[m * ta.stage_ld + t - lv.ta] + hbl[t - lv.ta]; };
+    if (sub == 0 && j > 0)
+      up = ((const double2*)(pst + state_units<P>(g, lv.ca) * (2 * M) * (long long)sizeof(S)))[t.pidx[m]];
+    const uint64_t y = t.ylds[m * W], yh = W == 2 ? t.ylds[m * W + 1] : 0ull;
+    auto bit = [&](int q) -> int { return (int)(((q < 64 ? y : yh) >> (q & 63)) & 1ull); };
+    auto out = [&](int q) { return t.stage[m * t.stage_ld + q - lv.ta] + t.hbl[q - lv.ta]; };
     const bool constrained = g.n_up >= 0 && g.n_dn >= 0;
     double sum = 0.0;
     int bad = 0;
     const int tend = leaf ? n : lv.tb;
-    for (int t = lv.ta + sub; t < tend; t += TPR) {
-      const S o = out(t);
-      const int b = bit(t);
-      const int sp = (int)(((t < 64 ? g.spin_pos[1] : g.spin_pos_hi[1]) >> (t & 63)) & 1ull);
-      bool fr = true;
-      if (constrained) {
-        // ones among the earlier positions of this spin, and its later positions
-        const uint64_t m0 = sp ? g.spin_pos[1] : g.spin_pos[0];
-        const uint64_t low0 = t >= 64 ? ~0ull : (1ull << t) - 1;
-        int before = __popcll(y & m0 & low0), rem = __popcll(m0 & ~low0);
-        if constexpr (W == 2) {
-          const uint64_t m1 = sp ? g.spin_pos_hi[1] : g.spin_pos_hi[0];
-          const uint64_t low1 = t <= 64 ? 0ull : (1ull << (t - 64)) - 1;
-          before += __popcll(yh & m1 & low1);
-          rem += __popcll(m1 & ~low1);
-        }
-        rem -= 1;                                        // position t itself
-        const int ns = sp ? g.n_dn : g.n_up;
-        const bool f0 = before >= ns, f1 = before + rem < ns;
-        bad |= (f0 && b) || (f1 && !b);
-        fr = !(f0 || f1);
-      }
-      if (fr) sum -= (double)softplus<S>(b ? -o : o);
+    for (int q = lv.ta + sub; q < tend; q += TPR) {
+      const S o = out(q);
+      const int b = bit(q);
+      bool f0 = false, f1 = false;
+      if (constrained) forced<W>(g, y, yh, q, spin_at(g, q), f0, f1);
+      bad |= (f0 && b) || (f1 && !b);
+      if (!(f0 || f1)) sum -= (double)softplus<S>(b ? -o : o);
     }
 #pragma unroll
     for (int off = TPR / 2; off >= 1; off >>= 1) {
@@ -530,7 +594,8 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
       sum += up.x;
       bad |= up.y != 0.0;
       if (!leaf) {
-        ((double2*)(st + state_units<P>(g, cb) * (2 * M) * (long long)sizeof(S)))[half + m] = make_double2(sum, bad ? 1.0 : 0.0);
+        ((double2*)(st + state_units<P>(g, lv.cb) * (2 * M) * (long long)sizeof(S)))[half + m] =
+            make_double2(sum, bad ? 1.0 : 0.0);
       } else if (m < c) {
         const double la = bad ? -INFINITY : 0.5 * sum;
         if (g.net_kind == 1) ta.out[2 * (row0 + m)] = la;
@@ -597,15 +662,8 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
           tp += b;
         }
         if (fn && at < M) {
-          pidx[at] = ip & (2 * M - 1);
-          if constexpr (W == 1) {
-            ylds[at] = __builtin_bitreverse64(xs[r]) >> (64 - n);
-          } else {
-            const uint64_t r0 = __builtin_bitreverse64(xs[2 * r + 1]), r1 = __builtin_bitreverse64(xs[2 * r]);
-            const int sh = 128 - n;
-            ylds[2 * at] = sh == 0 ? r0 : ((r0 >> sh) | (r1 << (64 - sh)));
-            ylds[2 * at + 1] = r1 >> sh;
-          }
+          t.pidx[at] = ip & (2 * M - 1);
+          t.put_prefix(at, xs + (long long)r * W, n);
         }
         if (fn && at == M) {
           nxt[0] = r;
@@ -626,9 +684,9 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
       const int np = cnt > M ? __builtin_amdgcn_readfirstlane(nxt[1]) : par;
       lds_barrier();
       if (tid >= c && tid < M) {                               // a tile's empty places repeat its first node
-        pidx[tid] = pidx[0];
+        t.pidx[tid] = t.pidx[0];
 #pragma unroll
-        for (int w = 0; w < W; ++w) ylds[tid * W + w] = ylds[w];
+        for (int w = 0; w < W; ++w) t.ylds[tid * W + w] = t.ylds[w];
       }
       if (tid == 0) {
         cur[j] = ce;
@@ -646,6 +704,45 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
   }
   if (ta.prof_slot && threadIdx.x == 0)
     atomicAdd((unsigned long long*)ta.prof_slot + kProfSlots, (unsigned long long)issued);
+}
+
+// One step of the sampler's walk: every entry of the buffer is a node whose
+// prefix is its bits so far.  Within a level, step t takes the entry's state at
+// the level's first unit (place anc[i]: the entry it descends from when the
+// state was written) and evaluates only the own units that position t reads:
+// cond[i] = (logit at t, forcing code).  Once the level's positions are drawn,
+// a step with t < 0 writes the states of the next level.  Row by row every
+// step evaluated the whole network: 94 us a step at 60 qubits, 1024 units and
+// 16,384 entries; now 26 us, the three steps that write states among them.
+template <int P, int W>
+__global__ __launch_bounds__(kThreads, 4) void sample_units(Geom g, StepArgs sa) {
+  using S = typename Kind<P>::S;
+  constexpr int M = 2 * Kind<P>::TB;
+  extern __shared__ uint4 smem[];
+  const TileLds<P, W> t(smem, sa.own_max, 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const S* biases = (const S*)((const char*)sa.packed + g.bias_byte);
+  const Weights wb = weights(g, sa.packed);
+  const long long rows = *sa.d_u < sa.umax ? *sa.d_u : sa.umax;
+  for (long long r0 = (long long)blockIdx.x * M; r0 < rows; r0 += (long long)gridDim.x * M) {
+    lds_barrier();
+    const int tid = thread_index();
+    const long long row = r0 + tid < rows ? r0 + tid : r0;
+    if (tid < M) {
+      t.put_prefix(tid, sa.x + row * W, g.n);
+      t.pidx[tid] = sa.ca == 0 ? 0 : sa.anc ? sa.anc[row] : (int)row;
+    }
+    lds_barrier();
+    tile_units<P, W>(g, t, wb, biases, sa.ksplit, wv,
+                     TileJob{sa.ca, sa.cb, sa.eb, sa.t < 0 ? 0 : sa.t, sa.t < 0 ? 0 : sa.t + 1, sa.t < 0, sa.pst,
+                             sa.nodes, sa.st, sa.nodes, (int)r0});
+    if (sa.t >= 0 && tid < M && r0 + tid < rows) {
+      const uint64_t y = t.ylds[tid * W], yh = W == 2 ? t.ylds[tid * W + 1] : 0ull;
+      bool f0 = false, f1 = false;
+      if (g.n_up >= 0 && g.n_dn >= 0) forced<W>(g, y, yh, sa.t, spin_at(g, sa.t), f0, f1);
+      sa.cond[row] = make_double2((double)(t.stage[tid] + t.hbl[0]), f1 ? 2.0 : f0 ? 1.0 : 0.0);
+    }
+  }
 }
 
 // ------------------------------------------------------------------ host side
@@ -724,11 +821,9 @@ bool plan_levels(const Geom& g, TreePlan& t) {
   return t.lds <= 160 * 1024;
 }
 
-template <int P, int W>
-void launch_w(const Geom& g, const TreePlan& t, const TreeArgs& a, int grid, hipStream_t s) {
-  auto kern = tree_forward<P, W>;
-  // the LDS opt-in, once per device ordinal, safe across threads
-  static std::atomic<unsigned long long> done{0};
+// The LDS opt-in of a kernel, once per device ordinal, safe across threads.
+template <typename K>
+void lds_opt_in(K kern, std::atomic<unsigned long long>& done) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   const unsigned long long bit = 1ull << (dev & 63);
@@ -736,10 +831,46 @@ void launch_w(const Geom& g, const TreePlan& t, const TreeArgs& a, int grid, hip
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     done.fetch_or(bit, std::memory_order_release);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), t.lds, s, g, a);
+}
+
+template <int P, int W>
+void launch_w(const Geom& g, const TreePlan& t, const TreeArgs& a, int grid, hipStream_t s) {
+  static std::atomic<unsigned long long> done{0};
+  lds_opt_in(tree_forward<P, W>, done);
+  hipLaunchKernelGGL((tree_forward<P, W>), dim3((unsigned)grid), dim3(kThreads), t.lds, s, g, a);
+}
+
+template <int P>
+void launch_step(const Geom& g, const TreePlan& t, const StepArgs& a, int grid, hipStream_t s) {
+  static std::atomic<unsigned long long> one{0}, two{0};
+  if (g.words == 2) {
+    lds_opt_in(sample_units<P, 2>, two);
+    hipLaunchKernelGGL((sample_units<P, 2>), dim3((unsigned)grid), dim3(kThreads), t.lds, s, g, a);
+  } else {
+    lds_opt_in(sample_units<P, 1>, one);
+    hipLaunchKernelGGL((sample_units<P, 1>), dim3((unsigned)grid), dim3(kThreads), t.lds, s, g, a);
+  }
 }
 
 }  // namespace
+
+size_t sample_state_bytes(const Geom& g, int cb, long long entries) {
+  const long long units = g.prec == P_F64 ? state_units<P_F64>(g, cb) : state_units<P_F32>(g, cb);
+  return (size_t)units * (size_t)entries * (g.prec == P_F64 ? 8 : 4);
+}
+
+void launch_sample_units(const Geom& g, const TreePlan& t, const StepArgs& sa, int cu_count, hipStream_t s) {
+  StepArgs a = sa;
+  a.own_max = t.args.own_max;
+  const int grid = (int)std::min<long long>((a.umax + t.rows - 1) / t.rows, 2LL * std::max(cu_count, 1));
+  switch (g.prec) {
+    case P_BF16: return launch_step<P_BF16>(g, t, a, grid, s);
+    case P_BF16X3: return launch_step<P_BF16X3>(g, t, a, grid, s);
+    case P_BF16W: return launch_step<P_BF16W>(g, t, a, grid, s);
+    case P_F32: return launch_step<P_F32>(g, t, a, grid, s);
+    case P_F64: return launch_step<P_F64>(g, t, a, grid, s);
+  }
+}
 
 bool tree_plan(const Geom& g, TreePlan& t) {
   if (g.order_kind != 2 || g.net_kind == 2) return false;

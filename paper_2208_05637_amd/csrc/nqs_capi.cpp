@@ -174,6 +174,7 @@ struct nqs_plan {
   size_t packed_phase = 0;
   bool tree = false;       // connected configurations take the prefix-shared forward
   TreePlan tp{};
+  bool levels = false;     // the network has such levels (tp): the sampler walks them
   double flops_alg_row = 0, flops_exec_row = 0;   // forward flops per configuration
   double flops_exec_phase_row = 0;                // of the second, the separate phase network's
   // profiling
@@ -858,7 +859,8 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
     const double rate = (g.prec == P_F64 ? 60e12 : g.prec == P_F32 ? 130e12 : 1100e12) / 256;
     const double rows = forward_rows_per_block(g.prec, g.h);
     const double waves = std::ceil((double)p->EC / (rows * std::max(ctx->cu_count, 1)));
-    p->tree = waves * (8e-6 + rows * p->flops_exec_row / rate) > 100e-6 && tree_plan(p->g, p->tp);
+    p->levels = tree_plan(p->g, p->tp);
+    p->tree = p->levels && waves * (8e-6 + rows * p->flops_exec_row / rate) > 100e-6;
   }
   *out = p;
   return NQS_OK;
@@ -1613,6 +1615,8 @@ nqs_status nqs_plan_kernel_info(const nqs_plan* p, int* waves_per_block, int* ro
 namespace {
 struct SampleLayout {
   size_t err, packed, cond, x, cnt, kx, kc, eq, keep, eqoff, koff, stmp, sel, du, dnk, total;
+  size_t anc[2], state[2], full;   // the walk's states come last: total is what a call needs, full what it can use
+  bool walk;                       // states of every level fit 32-bit offsets
 };
 
 SampleLayout sample_layout(const nqs_plan* p, int64_t U) {
@@ -1636,6 +1640,21 @@ SampleLayout sample_layout(const nqs_plan* p, int64_t U) {
   L.du = take(8);
   L.dnk = take(8);
   L.total = o;
+  L.walk = false;
+  if (p->levels && U <= kFoldEntries) {
+    // a level's states are read while the next level's are written
+    const long long places = (U + p->tp.rows - 1) / p->tp.rows * p->tp.rows;
+    size_t need[2] = {0, 0};
+    for (int j = 0; j + 1 < p->tp.args.nlev; ++j)
+      need[j & 1] = std::max(need[j & 1], sample_state_bytes(p->g, p->tp.args.lev[j].cb, places));
+    L.walk = std::max(need[0], need[1]) < (1ull << 32);
+    if (L.walk)
+      for (int k = 0; k < 2; ++k) {
+        L.anc[k] = take((size_t)U * 4);
+        L.state[k] = take(need[k]);
+      }
+  }
+  L.full = o;
   return L;
 }
 }  // namespace
@@ -1644,7 +1663,7 @@ nqs_status nqs_sample_workspace_size(const nqs_plan* p, int64_t max_unique, size
   if (!p || !bytes) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
   if (max_unique < 1 || max_unique > (1LL << 30))
     return fail(NQS_ERR_INVALID_ARGUMENT, "max_unique %lld outside 1..2^30", (long long)max_unique);
-  *bytes = sample_layout(p, max_unique).total;
+  *bytes = sample_layout(p, max_unique).full;
   return NQS_OK;
 }
 
@@ -1677,10 +1696,50 @@ nqs_status nqs_sample(nqs_plan* p, const float* params, int64_t n_draws, uint64_
   void* packed = at<void>(ws, L.packed);
   launch_pack_fused(p->g, params, packed, s);
   launch_sample_init(b.x, b.words, b.cnt, n_draws, b.d_u, s);
-  for (int t = 0; t < p->g.n; ++t) {
-    launch_forward_cond(p->g, p->variant, p->resident, p->ctx->cu_count, packed, b.x, max_unique, b.d_u, b.cond, t,
-                        s);
-    launch_sample_step(b, max_unique, t, (int)p->g.order[t], seed, s);
+  if (!L.walk || ws_bytes < L.full) {
+    for (int t = 0; t < p->g.n; ++t) {
+      launch_forward_cond(p->g, p->variant, p->resident, p->ctx->cu_count, packed, b.x, max_unique, b.d_u, b.cond, t,
+                          s);
+      launch_sample_step(b, max_unique, t, (int)p->g.order[t], seed, nullptr, nullptr, s);
+    }
+  } else {
+    // the entries as nodes of the prefix tree: level j serves the positions that
+    // its units see whole, then its states carry the entries into level j + 1
+    const TreeArgs& lv = p->tp.args;
+    const int TB = p->g.TB;
+    StepArgs a{};
+    a.packed = packed;
+    a.x = b.x;
+    a.d_u = b.d_u;
+    a.umax = max_unique;
+    a.cond = (double2*)b.cond;
+    a.nodes = (unsigned)((max_unique + p->tp.rows - 1) / p->tp.rows * p->tp.rows);
+    a.ksplit = tree_head_ksplit(p->g, forward_variant_waves(p->g.prec, p->g.h, p->variant),
+                                forward_variant_rows(p->g.prec, p->g.h, p->variant));
+    int j = 0, turn = 0;
+    for (int t = 0; t < p->g.n; ++t) {
+      if (j + 1 < lv.nlev && t == lv.lev[j].d) {
+        a.t = -1;
+        a.ca = lv.lev[j].ca;
+        a.cb = lv.lev[j].cb;
+        a.eb = lv.lev[j].eb;
+        a.st = at<char>(ws, L.state[j & 1]);
+        launch_sample_units(p->g, p->tp, a, p->ctx->cu_count, s);
+        a.pst = a.st;
+        a.anc = nullptr;
+        ++j;
+      }
+      a.t = t;
+      a.ca = lv.lev[j].ca;
+      a.cb = a.eb = std::max(a.ca, std::min(lv.lev[j].eb, (prefix_of_class(p->g, t) + TB - 1) / TB));
+      launch_sample_units(p->g, p->tp, a, p->ctx->cu_count, s);
+      int* next = at<int>(ws, L.anc[turn]);
+      launch_sample_step(b, max_unique, t, (int)p->g.order[t], seed, a.anc, next, s);
+      if (j > 0) {
+        a.anc = next;
+        turn ^= 1;
+      }
+    }
   }
   launch_sample_finish(b, max_unique, d_x, d_w, (long long*)d_n_unique, s);
   return launch_check("sample");

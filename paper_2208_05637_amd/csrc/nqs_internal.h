@@ -121,6 +121,25 @@ void launch_tree_forward(const Geom& g, const TreePlan& t, int ksplit, const voi
                          long long rows_bound, const long long* d_count, double* out, long long* prof_slot,
                          void* scratch, int grid, hipStream_t s);
 
+// One step of the sampler's walk over its entries (kernels_tree.hip): units of
+// blocks [ca, eb) from the states pst of the units before ca; t >= 0: cond[i] =
+// (logit at position t, code 0 free, 1 forced to 0, 2 forced to 1); t < 0: the
+// states of blocks [cb, NB) into st.  nodes: places per unit of the states.
+struct StepArgs {
+  const void* packed;
+  const uint64_t* x;
+  const long long* d_u;
+  long long umax;
+  const int* anc;      // place of entry i's state in pst; nullptr: i
+  const char* pst;
+  char* st;
+  double2* cond;
+  unsigned nodes;
+  int t, ca, cb, eb, ksplit, own_max;
+};
+size_t sample_state_bytes(const Geom& g, int cb, long long entries);
+void launch_sample_units(const Geom& g, const TreePlan& t, const StepArgs& sa, int cu_count, hipStream_t s);
+
 // backward: recompute the sample forward on S samples and accumulate the
 // gradient into grad (f64, flat parameter layout).  scratch holds
 // backward_scratch_elems(g, S) elements of the path's backward type
@@ -149,7 +168,12 @@ struct SampleBufs {
   int words;         // 64-bit words per configuration (x and kx hold `words` words each)
 };
 void launch_sample_init(uint64_t* x, int words, long long* cnt, long long n_draws, long long* d_u, hipStream_t s);
-void launch_sample_step(const SampleBufs& b, long long umax, int t, int q, uint64_t seed, hipStream_t s);
+// Children of the buffer's entries, and the new buffer of at most umax of them.
+// anc_in (nullptr: i), anc_out: a number per entry that its children inherit;
+// kept up to kFoldEntries entries.
+constexpr long long kFoldEntries = 131072;
+void launch_sample_step(const SampleBufs& b, long long umax, int t, int q, uint64_t seed, const int* anc_in,
+                        int* anc_out, hipStream_t s);
 void launch_sample_finish(const SampleBufs& b, long long umax, uint64_t* ox, double* ow, long long* on,
                           hipStream_t s);
 
