@@ -229,9 +229,13 @@ nqs_status nqs_net_param_count(const nqs_net_desc* net, int64_t* n_params);
    strings themselves) it also looks back one chunk: a chunk's distinct
    configurations that the previous chunk of the same call evaluated take that
    chunk's log psi instead of a forward row (the same values; the workspace
-   then holds two hash tables and two log psi sets). */
+   then holds two hash tables and two log psi sets).
+   A chunk with at least four times as many entries as its sector has
+   configurations (one word, at most 28 qubits, and the map of all of them no
+   larger than the chunk's log psi) evaluates each once with or without these
+   tables: its workspace and values are the same. */
 #define NQS_PLAN_DEDUP_ON   1u   /* deduplicate connected configurations per chunk */
-#define NQS_PLAN_DEDUP_OFF  2u   /* never deduplicate (default when no flag is set) */
+#define NQS_PLAN_DEDUP_OFF  2u   /* no hash tables (default when no flag is set) */
 #define NQS_PLAN_DEDUP_AUTO 4u   /* size the workspace for dedup, start with it on and
                                     let nqs_plan_autotune decide */
 

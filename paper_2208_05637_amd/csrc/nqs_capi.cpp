@@ -174,6 +174,7 @@ struct nqs_plan {
   size_t packed_phase = 0;
   bool tree = false;       // connected configurations take the prefix-shared forward
   TreePlan tp{};
+  int64_t sector = 0;      // configurations of the sector where a sector index can pay, else 0
   bool levels = false;     // the network has such levels (tp): the sampler walks them
   double flops_alg_row = 0, flops_exec_row = 0;   // forward flops per configuration
   double flops_exec_phase_row = 0;                // of the second, the separate phase network's
@@ -248,6 +249,18 @@ static WsLayout layout(const nqs_plan* p, int64_t B) {
   }
   L.full = o;
   return L;
+}
+
+// A walk down the tree takes a handful of tiles one after the other, 60 us and
+// more however few the rows; row by row they are one wave of tiles over the
+// CUs.  So rows that the row-by-row forward does in about 100 us stay with it
+// (12 qubits, FP64, 64 units, 30,000 rows: 9 us against 86).  Rates: what the
+// row-by-row kernels reach, per CU.
+static bool tree_pays(const nqs_plan* p, int64_t most_rows) {
+  const double rate = (p->g.prec == P_F64 ? 60e12 : p->g.prec == P_F32 ? 130e12 : 1100e12) / 256;
+  const double rows = forward_rows_per_block(p->g.prec, p->g.h);
+  const double waves = std::ceil((double)most_rows / (rows * std::max(p->ctx->cu_count, 1)));
+  return p->levels && waves * (8e-6 + rows * p->flops_exec_row / rate) > 100e-6;
 }
 
 // A workspace of `bytes` (at least total) may hold states for fewer
@@ -800,6 +813,8 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
     p->HT = ht;
     p->lookback = g.words == 1 && g.n < 64;
   }
+  if (g.words == 1 && g.n <= kSectorQubits)
+    p->sector = g.n_up < 0 ? 1ll << g.n : (int64_t)(binom((g.n + 1) / 2, g.n_up) * binom(g.n / 2, g.n_dn) + 0.5);
   p->Sb = std::min<int64_t>(max_batch, 4096);
   p->bw = g.prec == P_F64 ? 8 : 4;
   p->packed_bytes = packed_bytes_of(g);
@@ -850,18 +865,8 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
     p->flops_exec_phase_row = 2.0 * g.TB * g.KSTEP * (mult1 * (double)ph1 + mult * (double)ph);
     p->flops_exec_row = 2.0 * g.TB * g.KSTEP * (mult1 * (double)fr1 + mult * (double)fr) + p->flops_exec_phase_row;
   }
-  // A walk down the tree takes a handful of tiles one after the other, 60 us and
-  // more however few the rows; row by row they are one wave of tiles over the
-  // CUs.  So a chunk that the row-by-row forward does in about 100 us stays
-  // with it (12 qubits, FP64, 64 units, a chunk of 30,000 entries: 9 us against
-  // 86).  Rates: what the row-by-row kernels reach, per CU.
-  {
-    const double rate = (g.prec == P_F64 ? 60e12 : g.prec == P_F32 ? 130e12 : 1100e12) / 256;
-    const double rows = forward_rows_per_block(g.prec, g.h);
-    const double waves = std::ceil((double)p->EC / (rows * std::max(ctx->cu_count, 1)));
-    p->levels = tree_plan(p->g, p->tp);
-    p->tree = p->levels && waves * (8e-6 + rows * p->flops_exec_row / rate) > 100e-6;
-  }
+  p->levels = tree_plan(p->g, p->tp);
+  p->tree = tree_pays(p, p->EC);
   *out = p;
   return NQS_OK;
 }
@@ -985,7 +990,7 @@ static void forward_net(const nqs_plan* p, const void* packed, const uint64_t* x
 static void forward_connected(const nqs_plan* p, void* ws, const WsLayout& L, const void* packed, const uint64_t* x,
                               long long bound, const long long* d_count, double* out, long long* slot,
                               hipStream_t s) {
-  if (!L.tree_grid) {
+  if (!L.tree_grid || !tree_pays(p, bound)) {
     forward_net(p, packed, x, bound, d_count, out, slot, s);
     return;
   }
@@ -1023,7 +1028,18 @@ struct ChunkFwd {
   double* out;                // log psi of each
   double* lp;                 // log psi the reduce reads: per entry, or per distinct configuration with dedup
   bool gather;                // out holds only the configurations new to this chunk (look-back)
+  bool sector;                // entries find theirs by the sector index
 };
+
+// The sector index takes the place of one log psi per entry: it stands in that
+// buffer, with one per configuration.  It pays where a call's entries (their
+// bound: the count is the device's) are several times the sector and the map
+// of 2^n bytes fits; the hash tables keep the calls of several chunks, whose
+// look-back evaluates each configuration once for two chunks.
+static bool by_sector(const nqs_plan* p, int64_t Sc, int64_t B) {
+  return p->sector > 0 && std::min<int64_t>(Sc * p->Emax, p->EC) >= 4 * p->sector &&
+         sector_bytes(p->g.n, p->sector).total <= (size_t)p->EC * 16 && (!p->dedup || B <= p->S);
+}
 
 // Enumerate (and optionally deduplicate) the connected configurations of
 // samples [c0, c0 + Sc), chunk k of the call.  With look-back, chunks
@@ -1031,7 +1047,7 @@ struct ChunkFwd {
 // k - 1's table for its distinct configurations and evaluates only those the
 // previous chunk did not (each row's log psi depends on that row alone, so the
 // reused values are the ones the forward would give).
-static ChunkFwd enum_chunk(nqs_plan* p, const uint64_t* x, int64_t c0, int64_t Sc, int64_t k, void* ws,
+static ChunkFwd enum_chunk(nqs_plan* p, const uint64_t* x, int64_t B, int64_t c0, int64_t Sc, int64_t k, void* ws,
                            const WsLayout& L) {
   hipStream_t s = p->ctx->stream;
   const HamDev H = ham_dev(p);
@@ -1048,7 +1064,13 @@ static ChunkFwd enum_chunk(nqs_plan* p, const uint64_t* x, int64_t c0, int64_t S
   const long long* d_total = off + Sc * p->R;
   const int64_t bound = std::min<int64_t>(Sc * p->Emax, p->EC);
   double* lpe = at<double>(ws, L.lpe);
-  if (!p->dedup) return {xe, d_total, bound, lpe, lpe, false};
+  if (by_sector(p, Sc, B)) {
+    const SectorBytes b = sector_bytes(p->g.n, p->sector);
+    launch_sector_index(xe, d_total, p->EC, p->g.n, p->g.n_up, p->g.n_dn, b, lpe, s);
+    return {(const uint64_t*)((char*)lpe + b.xu), (const long long*)((char*)lpe + b.tile) + b.tiles, p->sector, lpe,
+            lpe, false, true};
+  }
+  if (!p->dedup) return {xe, d_total, bound, lpe, lpe, false, false};
   uint64_t* xu = at<uint64_t>(ws, L.xu);
   long long* nu = at<long long>(ws, L.nu);
   const bool odd = p->lookback && (k & 1);
@@ -1056,12 +1078,12 @@ static ChunkFwd enum_chunk(nqs_plan* p, const uint64_t* x, int64_t c0, int64_t S
   launch_dedup(xe, p->g.words, p->g.n == 64, d_total, p->EC, at<void>(ws, odd ? L.htab2 : L.htab), p->HT, false,
                at<int>(ws, L.eu), xu, nu, at<int>(ws, L.dfirst), at<long long>(ws, L.drank),
                at<long long>(ws, L.drtmp), err, s);
-  if (!p->lookback || k == 0) return {xu, nu, bound, lp, lp, false};
+  if (!p->lookback || k == 0) return {xu, nu, bound, lp, lp, false, false};
   // the entries are dead once deduplicated: xe takes the new configurations
   long long* nnew = at<long long>(ws, L.nnew);
   launch_lookback(xu, nu, p->EC, at<void>(ws, odd ? L.htab : L.htab2), p->HT, at<int>(ws, L.src),
                   at<int>(ws, L.dfirst), at<long long>(ws, L.drank), at<long long>(ws, L.drtmp), xe, nnew, s);
-  return {xe, nnew, bound, at<double>(ws, L.lpn), lp, true};
+  return {xe, nnew, bound, at<double>(ws, L.lpn), lp, true, false};
 }
 
 // After the chunk's forward: with look-back, the distinct configurations' log
@@ -1078,7 +1100,8 @@ static void reduce_chunk(nqs_plan* p, int64_t c0, int64_t Sc, const ChunkFwd& cf
                          double* eloc) {
   const int hs = p->ham->has_imag ? 2 : 1;
   launch_reduce(Sc, p->R, at<long long>(ws, L.off), p->EC, at<double>(ws, L.diag), at<double>(ws, L.he), hs,
-                p->dedup ? at<int>(ws, L.eu) : nullptr, cf.lp, at<double>(ws, L.lps) + 2 * c0, eloc + 2 * c0,
+                p->dedup && !cf.sector ? at<int>(ws, L.eu) : nullptr, at<uint64_t>(ws, L.xe),
+                cf.sector ? (const SectorRec*)((char*)cf.lp + sector_bytes(p->g.n, p->sector).rec) : nullptr, p->g.n, cf.lp, at<double>(ws, L.lps) + 2 * c0, eloc + 2 * c0,
                 at<double>(ws, L.rpart), at<unsigned>(ws, L.err), p->ctx->stream);
 }
 
@@ -1090,7 +1113,7 @@ static nqs_status run_local_energy(nqs_plan* p, const float* params, const uint6
   forward_profiled(p, ws, L, packed, x, B, nullptr, at<double>(ws, L.lps), false);
   for (int64_t c0 = 0, k = 0; c0 < B; c0 += p->S, ++k) {
     const int64_t Sc = std::min<int64_t>(p->S, B - c0);
-    const ChunkFwd cf = enum_chunk(p, x, c0, Sc, k, ws, L);
+    const ChunkFwd cf = enum_chunk(p, x, B, c0, Sc, k, ws, L);
     forward_profiled(p, ws, L, packed, cf.x, cf.bound, cf.d_count, cf.out, true);
     finish_chunk(p, cf, ws, L);
     reduce_chunk(p, c0, Sc, cf, ws, L, eloc);
@@ -1337,12 +1360,12 @@ nqs_status nqs_energy_grad_multi(int n_inst, const nqs_instance* inst, void* ws,
       const int64_t c0 = r * p->S;
       if (c0 >= inst[i].B) continue;
       const int64_t Sc = std::min<int64_t>(p->S, inst[i].B - c0);
-      const ChunkFwd cf = enum_chunk(p, inst[i].d_samples, c0, Sc, r, W[i], L[i]);
+      const ChunkFwd cf = enum_chunk(p, inst[i].d_samples, inst[i].B, c0, Sc, r, W[i], L[i]);
       rid.push_back(i);
       c0s.push_back(c0);
       scs.push_back(Sc);
       cfs.push_back(cf);
-      if (L[i].tree_grid)
+      if (L[i].tree_grid && tree_pays(p, cf.bound))
         forward_connected(p, W[i], L[i], at<void>(W[i], L[i].packed), cf.x, cf.bound, cf.d_count, cf.out, nullptr, s);
       else
         add_segs(i, cf.x, cf.d_count, cf.out, cf.bound, ids, segs);
@@ -1808,7 +1831,7 @@ nqs_status nqs_reduce_table(nqs_plan* p, int64_t B, const double* lps, const dou
   if (B == 0) return launch_check("reduce");
   long long* off = at<long long>(ws, L.off);
   launch_seg_offsets(esample, n_entries, B, off, s);
-  launch_reduce(B, 1, off, n_entries, diag, eh, 2, nullptr, lpe, lps, eloc, at<double>(ws, L.rpart), err, s);
+  launch_reduce(B, 1, off, n_entries, diag, eh, 2, nullptr, nullptr, nullptr, p->g.n, lpe, lps, eloc, at<double>(ws, L.rpart), err, s);
   return launch_check("reduce");
 }
 

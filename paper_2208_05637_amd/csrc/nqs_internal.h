@@ -71,11 +71,31 @@ void launch_lookback(const uint64_t* xu, const long long* d_nu, long long cap, c
 void launch_lookback_gather(const long long* d_nu, long long cap, const int* src, const long long* rank,
                             const double* lp_prev, const double* lp_new, double* lp, hipStream_t s);
 
-// partials holds reduce_partials_elems(S) doubles
+// Distinct configurations of the entries by their place in a map of all 2^n
+// configurations (one-word strings, n <= kSectorQubits), from a base address
+// on: log psi of `configs` configurations (the sector's number), their list in
+// ascending order, a record per 64 places (its set bits and the number of the
+// first), the tiles' numbers, tile[tiles] the number of all of them, the map.
+constexpr int kSectorQubits = 28;
+constexpr int kSectorTile = 4096;
+struct alignas(16) SectorRec {
+  unsigned long long bits;
+  int base, pad;
+};
+struct SectorBytes {
+  long long tiles;
+  size_t xu, rec, tile, seen, total;
+};
+SectorBytes sector_bytes(int n, long long configs);
+void launch_sector_index(const uint64_t* xe, const long long* d_count, long long cap, int n, int n_up, int n_dn,
+                         const SectorBytes& b, void* base, hipStream_t s);
+
+// partials holds reduce_partials_elems(S) doubles; log psi of entry e is
+// lpe[eu[e]] with eu, lpe[number of xe[e]] with rec (a sector index), else lpe[e]
 long long reduce_partials_elems(long long S);
 void launch_reduce(long long S, int R, const long long* off, long long cap, const double* diag,
-                   const double* he, int hstride, const int* eu, const double* lpe,
-                   const double* lps, double* eloc, double* partials, unsigned* err, hipStream_t s);
+                   const double* he, int hstride, const int* eu, const uint64_t* xe, const SectorRec* rec, int n,
+                   const double* lpe, const double* lps, double* eloc, double* partials, unsigned* err, hipStream_t s);
 void launch_energy(const double* eloc, const double* w, long long B, double* energy,
                    unsigned* err, hipStream_t s);
 
