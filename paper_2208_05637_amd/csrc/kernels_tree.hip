@@ -564,11 +564,16 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
                              2 * M, st, 2 * M, half});
 
     // ------------------------------------------------- log-sigmoids, phase
-    constexpr int TPR = kThreads / M;
-    const int tid = thread_index();
-    const int m = tid / TPR, sub = tid % TPR;
+    // A lane takes a node and a wave every eighth position (FP64, whose tiles
+    // fill half a wave: two in sixteen), so what a position asks of all nodes
+    // alike (its spin, the masks of the earlier positions) is scalar work: of
+    // 190 vector instructions a position and node 135 are left, 117 of them
+    // log1pf.  (With a node's positions on eight lanes: 400 samples at 64
+    // qubits, L = 3, 512 units, 31.4 ms, now 29.9.)
+    constexpr int NPW = 64 / M, NSUB = kWaves * NPW;
+    const int tid = thread_index(), m = tid % M, sub = wv * NPW + (NPW > 1 ? (tid & 63) / M : 0);
     double2 up = make_double2(0.0, 0.0);                       // what the parent has summed
-    if (sub == 0 && j > 0)
+    if (tid < M && j > 0)
       up = ((const double2*)(pst + state_units<P>(g, lv.ca) * (2 * M) * (long long)sizeof(S)))[t.pidx[m]];
     const uint64_t y = t.ylds[m * W], yh = W == 2 ? t.ylds[m * W + 1] : 0ull;
     auto bit = [&](int q) -> int { return (int)(((q < 64 ? y : yh) >> (q & 63)) & 1ull); };
@@ -576,8 +581,10 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
     const bool constrained = g.n_up >= 0 && g.n_dn >= 0;
     double sum = 0.0;
     int bad = 0;
+    uint64_t ahead = 0;                                        // brings the next tile's rows into L2
+    if (leaf && wv == kWaves - 1 && row0 + M + m < rows) ahead = ta.x[(row0 + M + m) * W];
     const int tend = leaf ? n : lv.tb;
-    for (int q = lv.ta + sub; q < tend; q += TPR) {
+    for (int q = lv.ta + sub; q < tend; q += NSUB) {
       const S o = out(q);
       const int b = bit(q);
       bool f0 = false, f1 = false;
@@ -585,14 +592,23 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
       bad |= (f0 && b) || (f1 && !b);
       if (!(f0 || f1)) sum -= (double)softplus<S>(b ? -o : o);
     }
+    asm volatile("" ::"v"(ahead));
+    // the partial sums, in the place of the activations: none is positive, so 1 stands for a contradiction
+    double* part = (double*)t.act;
+    part[sub * M + m] = bad ? 1.0 : sum;
+    lds_barrier();
+    if (tid < M) {
+      double v[NSUB];
 #pragma unroll
-    for (int off = TPR / 2; off >= 1; off >>= 1) {
-      sum += __shfl_xor(sum, off);
-      bad |= __shfl_xor(bad, off);
-    }
-    if (sub == 0) {
-      sum += up.x;
-      bad |= up.y != 0.0;
+      for (int i = 0; i < NSUB; ++i) v[i] = part[i * M + m];
+      bad = up.y != 0.0;
+#pragma unroll
+      for (int i = 0; i < NSUB; ++i) bad |= v[i] > 0.0;
+#pragma unroll
+      for (int off = NSUB / 2; off >= 1; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < off; ++i) v[i] += v[i + off];
+      sum = v[0] + up.x;
       if (!leaf) {
         ((double2*)(st + state_units<P>(g, lv.cb) * (2 * M) * (long long)sizeof(S)))[half + m] =
             make_double2(sum, bad ? 1.0 : 0.0);
@@ -617,31 +633,57 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
     const uint64_t* xs = ta.x + s0 * W;
     const int last = ta.nlev - 1;
     lds_barrier();
-    if (thread_index() <= last) {
+    int lc = 0, lpar = -1;                                     // the last level's cursors, in registers
+    if (thread_index() < last) {
       cur[thread_index()] = 0;                                 // rows covered
       pb[thread_index()] = -1;                                 // last node of the level above that started before cur
       tiles[thread_index()] = 0;
     }
     for (int j = 0;;) {
+      if (j == last) {
+        // Every row is a node, so one wave collects a tile; the others are past
+        // the last use of the tile before (its partial sums' barrier).  Like
+        // the levels above, with rows to be counted over all waves, five
+        // barriers: 29.9 ms where this takes 28.4 (64 qubits, 400 samples).
+        const int lim = __builtin_amdgcn_readfirstlane(cur[j - 1]);
+        if (lc == len) break;                                  // (the levels above wait for the last one)
+        const int c = lim - lc < M ? lim - lc : M;
+        if (lim < len && c < M) {
+          --j;
+          continue;
+        }
+        if (wv == 0) {
+          const int lane = thread_index(), r = lc + lane;
+          const bool in = lane < c;
+          const bool fp = in && (r == 0 || common_prefix<W>(xs, r, n) < ta.lev[j - 1].d);
+          const unsigned long long bp = __ballot(fp);
+          const int ip = lpar + __popcll(bp & ((2ull << lane) - 1));
+          const int first = __builtin_amdgcn_readfirstlane(ip);
+          if (lane < M) {                                      // a tile's empty places repeat its first node
+            t.pidx[lane] = (in ? ip : first) & (2 * M - 1);
+            t.put_prefix(lane, xs + (long long)(in ? r : lc) * W, n);
+          }
+          lpar += __popcll(bp);
+        }
+        lds_barrier();
+        issued += ta.lev[j].flops;
+        tile(j, c, 0, s0 + lc);
+        lc += c;
+        continue;
+      }
       lds_barrier();
       const int tid = thread_index(), lane = tid & 63;
       const int c0 = __builtin_amdgcn_readfirstlane(cur[j]);
       const int lim = j > 0 ? __builtin_amdgcn_readfirstlane(cur[j - 1]) : len;
-      const bool leaf = j == last;
-      if (c0 == len) break;                                    // (the last level: the others wait for it)
-      if (leaf && lim < len && lim - c0 < M) {
-        --j;
-        continue;
-      }
       // Nodes start at rows that differ from the row before within the level's
       // positions; a node's parent is the last node of the level above to start.
-      const int dn = leaf ? 0 : ta.lev[j].d, dp = j > 0 ? ta.lev[j - 1].d : 0;
+      const int dn = ta.lev[j].d, dp = j > 0 ? ta.lev[j - 1].d : 0;
       int cnt = 0, par = __builtin_amdgcn_readfirstlane(pb[j]), buf = 0;
       for (int b0 = c0; b0 < lim && cnt <= M; b0 += kThreads) {
         const int r = b0 + tid;
         const bool in = r < lim;
         const int cp = in && r > 0 ? common_prefix<W>(xs, r, n) : 0;
-        const bool fn = in && (leaf || cp < dn), fp = in && cp < dp;
+        const bool fn = in && cp < dn, fp = in && cp < dp;
         const unsigned long long bn = __ballot(fn), bp = __ballot(fp);
         const unsigned long long below = (1ull << lane) - 1;
         if (lane == 0) {
@@ -696,10 +738,8 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
       lds_barrier();
       issued += ta.lev[j].flops;
       tile(j, c, half, s0 + c0);
-      if (!leaf) {
-        __syncthreads();                                       // the states are written
-        ++j;
-      }
+      __syncthreads();                                         // the states are written
+      ++j;
     }
   }
   if (ta.prof_slot && threadIdx.x == 0)
