@@ -114,20 +114,57 @@ __device__ __forceinline__ bool sector_ok(const Bits<W>& x, const Bits<W>& f) {
   return 2 * xu == fu && 2 * xd == fd;
 }
 
+// The empty flip's h: one wave per sample, whose lanes fetch and sign 64 terms
+// at a time; the sum itself stays sequential in canonical order.  Bound by that
+// chain of FP64 additions; with one thread per sample, every term's loads were
+// part of it (250 samples at 76 qubits, 2,926 terms: 490 us, now 45).
+__device__ __forceinline__ double lane_value(double v, int l) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, l), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), l);
+  return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
 template <bool IMAG, int W>
-__global__ void diag_kernel(HamDev H, const uint64_t* __restrict__ xs, long long S,
-                            double* __restrict__ diag) {
-  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void diag_kernel(HamDev H, const uint64_t* __restrict__ xs, long long S,
+                                                   double* __restrict__ diag) {
+  const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) >> 6;
+  const int lane = threadIdx.x & 63;
   if (i >= S) return;
   double re = 0.0, im = 0.0;
-  if (H.gfirst) group_value<IMAG, W>(H, load_bits<W>(xs, i), 0, re, im);
-  diag[2 * i] = re;
-  diag[2 * i + 1] = im;
+  if (H.gfirst) {
+    const Bits<W> x = load_bits<W>(xs, i);
+    const long long k0 = H.tables ? H.soff[0] : H.goff[0], k1 = H.tables ? H.soff[1] : H.goff[1];
+    for (long long kb = k0; kb < k1; kb += 64) {
+      const int cnt = k1 - kb < 64 ? (int)(k1 - kb) : 64;
+      double a = 0.0, b = 0.0;
+      if (lane < cnt) {
+        const long long k = kb + lane, e = H.tables ? H.stab[k] : k;   // the empty flip's tables have one entry each
+        const unsigned long long par = (unsigned long long)(popc_and<W>(x, H.tables ? H.su : H.tz, k) & 1) << 63;
+        a = __longlong_as_double(__double_as_longlong((H.tables ? H.tabre : H.tre)[e]) ^ par);
+        if constexpr (IMAG) b = __longlong_as_double(__double_as_longlong((H.tables ? H.tabim : H.tim)[e]) ^ par);
+      }
+      if (cnt == 64) {
+#pragma unroll
+        for (int t = 0; t < 64; ++t) {
+          re += lane_value(a, t);
+          if constexpr (IMAG) im += lane_value(b, t);
+        }
+      } else {
+        for (int t = 0; t < cnt; ++t) {
+          re += lane_value(a, t);
+          if constexpr (IMAG) im += lane_value(b, t);
+        }
+      }
+    }
+  }
+  if (lane == 0) {
+    diag[2 * i] = re;
+    diag[2 * i + 1] = im;
+  }
 }
 
 void launch_diag(const HamDev& H, const uint64_t* x, long long S, double* diag, hipStream_t s) {
   if (S <= 0) return;
-  unsigned blocks = (unsigned)((S + 255) / 256);
+  unsigned blocks = (unsigned)((S + 3) / 4);
   if (H.words == 2) {
     if (H.tim) hipLaunchKernelGGL((diag_kernel<true, 2>), dim3(blocks), dim3(256), 0, s, H, x, S, diag);
     else hipLaunchKernelGGL((diag_kernel<false, 2>), dim3(blocks), dim3(256), 0, s, H, x, S, diag);
@@ -330,19 +367,20 @@ __global__ void write_kernel(HamDev H, const uint64_t* __restrict__ xs, long lon
 }
 
 // The same entries from the term list, with the work turned around: a
-// workgroup takes kWsSamples samples and one group range, stages the range's
+// workgroup takes NS samples and one group range, stages the range's
 // groups and terms in LDS in batches (coalesced loads, shared by its samples),
 // and each wave walks its samples one at a time with its lanes on 64
 // consecutive groups.  A ballot over the kept groups and a prefix count give
 // every kept group its place in the sample's segment, so each store
 // instruction writes consecutive entries.  h_g(x) is the same sequential sum
 // over the group's terms as group_h.
-constexpr int kWsSamples = 64;              // samples per workgroup
+// NS = 64 samples share a staged batch; 16 where workgroups of 64 would leave
+// CUs without one.
 constexpr int kWsWaves = 4;                 // waves per workgroup
 constexpr int kWsGroups = 448;              // groups per staged batch (four workgroups per CU in LDS)
 constexpr int kWsTerms = 2048;              // terms per staged batch (and the largest group it takes)
 
-template <bool IMAG, int W>
+template <bool IMAG, int W, int NS>
 __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
     HamDev H, const uint64_t* __restrict__ xs, long long S, int R, int gper, const long long* __restrict__ off,
     long long cap, uint64_t* __restrict__ xe, double* __restrict__ he, int* __restrict__ esample, int hstride,
@@ -354,13 +392,13 @@ __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
   __shared__ double lim[IMAG ? kWsTerms : 1];
   __shared__ int lkept[kWsWaves][128];   // per wave: kept groups awaiting evaluation
   __shared__ int lge;
-  constexpr int SPW = kWsSamples / kWsWaves;   // samples per wave
+  constexpr int SPW = NS / kWsWaves;   // samples per wave
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r = blockIdx.y;
   const int g0 = H.gfirst + r * gper;
   const int g1 = min(H.G, g0 + gper);
   // lane j < SPW holds sample j of this wave: its bits and its write position
-  const long long i_l = (long long)blockIdx.x * kWsSamples + wv * SPW + (lane < SPW ? lane : 0);
+  const long long i_l = (long long)blockIdx.x * NS + wv * SPW + (lane < SPW ? lane : 0);
   const bool live_l = lane < SPW && i_l < S;
   Bits<W> x_l = load_bits<W>(xs, live_l ? i_l : 0);
   long long pos_l = live_l ? off[i_l * R + r] : 0;
@@ -391,7 +429,7 @@ __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
     }
     __syncthreads();
     for (int j = 0; j < SPW; ++j) {
-      const long long i = (long long)blockIdx.x * kWsSamples + wv * SPW + j;
+      const long long i = (long long)blockIdx.x * NS + wv * SPW + j;
       if (i >= S) break;
       Bits<W> x;
 #pragma unroll
@@ -506,23 +544,27 @@ static void launch_write_w(const HamDev& H, const uint64_t* x, long long S, int 
                        he, esample, hstride, err);
 }
 
+bool write_by_wave(bool tables, long long max_gterms) { return !tables && max_gterms <= kWsTerms; }
+
+template <int W, int NS>
+static void launch_write_staged(const HamDev& H, const uint64_t* x, long long S, int R, int gper,
+                                const long long* off, long long cap, uint64_t* xe, double* he, int* esample,
+                                int hstride, unsigned* err, hipStream_t s) {
+  const dim3 grid((unsigned)((S + NS - 1) / NS), (unsigned)R), block(64 * kWsWaves);
+  if (H.tim) hipLaunchKernelGGL((write_staged_kernel<true, W, NS>), grid, block, 0, s, H, x, S, R, gper, off, cap, xe,
+                                he, esample, hstride, err);
+  else hipLaunchKernelGGL((write_staged_kernel<false, W, NS>), grid, block, 0, s, H, x, S, R, gper, off, cap, xe,
+                          he, esample, hstride, err);
+}
+
 void launch_write(const HamDev& H, const uint64_t* x, long long S, int R, int gper,
                   const long long* off, long long cap, uint64_t* xe, double* he, int* esample,
                   int hstride, unsigned* err, hipStream_t s) {
   if (S <= 0) return;
-  if (!H.tables && H.max_gterms <= kWsTerms) {
-    const dim3 grid((unsigned)((S + kWsSamples - 1) / kWsSamples), (unsigned)R), block(64 * kWsWaves);
-    if (H.words == 2) {
-      if (H.tim) hipLaunchKernelGGL((write_staged_kernel<true, 2>), grid, block, 0, s, H, x, S, R, gper, off, cap, xe,
-                                    he, esample, hstride, err);
-      else hipLaunchKernelGGL((write_staged_kernel<false, 2>), grid, block, 0, s, H, x, S, R, gper, off, cap, xe,
-                              he, esample, hstride, err);
-    } else {
-      if (H.tim) hipLaunchKernelGGL((write_staged_kernel<true, 1>), grid, block, 0, s, H, x, S, R, gper, off, cap, xe,
-                                    he, esample, hstride, err);
-      else hipLaunchKernelGGL((write_staged_kernel<false, 1>), grid, block, 0, s, H, x, S, R, gper, off, cap, xe,
-                              he, esample, hstride, err);
-    }
+  if (write_by_wave(H.tables, H.max_gterms)) {
+    auto go = (S + 63) / 64 * R >= 512 ? (H.words == 2 ? launch_write_staged<2, 64> : launch_write_staged<1, 64>)
+                                       : (H.words == 2 ? launch_write_staged<2, 16> : launch_write_staged<1, 16>);
+    go(H, x, S, R, gper, off, cap, xe, he, esample, hstride, err, s);
     return;
   }
   if (H.words == 2) launch_write_w<2>(H, x, S, R, gper, off, cap, xe, he, esample, hstride, err, s);
@@ -1106,13 +1148,27 @@ struct Comp {
   __device__ double value() const { return s + c; }
 };
 
-// E_loc(x_i) = diag_i + sum_e h_e exp(lp(x'_e) - lp(x_i)).  Each sample's
-// entries are cut into kReduceSlices equal slices, one workgroup each
-// (enough workgroups to keep every CU streaming); a slice is summed with
-// per-thread compensation and a fixed tree, and the slices are then added to
-// the diagonal in slice order.  The cut depends only on the sample's own
-// entry range, so the result does not depend on scheduling or chunking.
+// E_loc(x_i) = diag_i + sum_e h_e exp(lp(x'_e) - lp(x_i)).  A sample's entries
+// are cut into up to kReduceSlices equal slices of about kReduceEntries and
+// more, one workgroup each (enough workgroups to keep every CU busy); a slice
+// is summed with per-thread compensation and a fixed tree, and the slices are
+// then added to the diagonal in slice order.  The cut depends only on the
+// sample's own number of entries, so the result does not depend on scheduling
+// or chunking.  Bound by FP64 exp and sincos: 204 us for 14.9 million entries
+// of 8,192 samples (with eight slices for every sample and the tree in LDS 245),
+// 30 us for 1.26 million of 3,500 samples (81).
 constexpr int kReduceSlices = 8;
+constexpr int kReduceEntries = 1024;
+
+__device__ __forceinline__ int reduce_slices(long long entries) {
+  const long long k = (entries + kReduceEntries - 1) / kReduceEntries;
+  return k > kReduceSlices ? kReduceSlices : (int)k;
+}
+__device__ __forceinline__ Comp shfl_merge(Comp x) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) x.merge(Comp{__shfl_down(x.s, d), __shfl_down(x.c, d)});
+  return x;
+}
 
 __global__ __launch_bounds__(256) void reduce_part_kernel(long long S, int R, const long long* __restrict__ off,
                                                           long long cap, const double* __restrict__ he,
@@ -1122,15 +1178,17 @@ __global__ __launch_bounds__(256) void reduce_part_kernel(long long S, int R, co
                                                           const double2* __restrict__ lpe,
                                                           const double2* __restrict__ lps,
                                                           double* __restrict__ partials) {
-  __shared__ double red[4][256];
-  const long long i = blockIdx.x / kReduceSlices;
-  const int part = (int)(blockIdx.x % kReduceSlices);
-  if (i >= S) return;
+  __shared__ double red[4][4];
+  // slice by slice, so that samples of one slice spread over all XCDs
+  const int part = (int)(blockIdx.x / S);
+  const long long i = blockIdx.x % S;
   long long a = off[i * R];
   long long b = off[(i + 1) * R];
   if (a > cap) a = cap;
   if (b > cap) b = cap;
-  const long long per = (b - a + kReduceSlices - 1) / kReduceSlices;
+  const int ns = reduce_slices(b - a);
+  if (part >= ns) return;
+  const long long per = (b - a + ns - 1) / ns;
   const long long pa = a + part * per;
   const long long pb = pa + per < b ? pa + per : b;
   const double2 ls = lps[i];
@@ -1152,34 +1210,39 @@ __global__ __launch_bounds__(256) void reduce_part_kernel(long long S, int R, co
     cr.add(mag * (hr * cs - hi * sn));
     ci.add(mag * (hr * sn + hi * cs));
   }
-  red[0][threadIdx.x] = cr.s;
-  red[1][threadIdx.x] = cr.c;
-  red[2][threadIdx.x] = ci.s;
-  red[3][threadIdx.x] = ci.c;
-  __syncthreads();
-  for (int d = 128; d >= 1; d >>= 1) {
-    if ((int)threadIdx.x < d) {
-      Comp x{red[0][threadIdx.x], red[1][threadIdx.x]}, y{red[0][threadIdx.x + d], red[1][threadIdx.x + d]};
-      x.merge(y);
-      red[0][threadIdx.x] = x.s;
-      red[1][threadIdx.x] = x.c;
-      Comp p{red[2][threadIdx.x], red[3][threadIdx.x]}, q{red[2][threadIdx.x + d], red[3][threadIdx.x + d]};
-      p.merge(q);
-      red[2][threadIdx.x] = p.s;
-      red[3][threadIdx.x] = p.c;
-    }
-    __syncthreads();
+  cr = shfl_merge(cr);
+  ci = shfl_merge(ci);
+  if ((threadIdx.x & 63) == 0) {
+    double* q = red[threadIdx.x >> 6];
+    q[0] = cr.s;
+    q[1] = cr.c;
+    q[2] = ci.s;
+    q[3] = ci.c;
   }
-  if (threadIdx.x < 4) partials[(i * kReduceSlices + part) * 4 + threadIdx.x] = red[threadIdx.x][0];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) {
+      cr.merge(Comp{red[w][0], red[w][1]});
+      ci.merge(Comp{red[w][2], red[w][3]});
+    }
+    double* q = partials + (i * kReduceSlices + part) * 4;
+    q[0] = cr.s;
+    q[1] = cr.c;
+    q[2] = ci.s;
+    q[3] = ci.c;
+  }
 }
 
-__global__ void reduce_combine_kernel(long long S, const double* __restrict__ diag,
+__global__ void reduce_combine_kernel(long long S, int R, const long long* __restrict__ off, long long cap,
+                                      const double* __restrict__ diag,
                                       const double2* __restrict__ lps, const double* __restrict__ partials,
                                       double* __restrict__ eloc, unsigned* err) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= S) return;
   Comp tr{diag[2 * i], 0.0}, ti{diag[2 * i + 1], 0.0};
-  for (int k = 0; k < kReduceSlices; ++k) {
+  const long long a = off[i * R] < cap ? off[i * R] : cap, b = off[(i + 1) * R] < cap ? off[(i + 1) * R] : cap;
+  const int ns = reduce_slices(b - a);
+  for (int k = 0; k < ns; ++k) {
     const double* q = partials + (i * kReduceSlices + k) * 4;
     tr.merge(Comp{q[0], q[1]});
     ti.merge(Comp{q[2], q[3]});
@@ -1202,7 +1265,7 @@ void launch_reduce(long long S, int R, const long long* off, long long cap, cons
   if (S <= 0) return;
   hipLaunchKernelGGL(reduce_part_kernel, dim3((unsigned)(S * kReduceSlices)), dim3(256), 0, s, S, R, off, cap,
                      he, hstride, eu, xe, rec, n < 64 ? (1ull << n) - 1 : ~0ull, (const double2*)lpe, (const double2*)lps, partials);
-  hipLaunchKernelGGL(reduce_combine_kernel, dim3((unsigned)((S + 255) / 256)), dim3(256), 0, s, S, diag,
+  hipLaunchKernelGGL(reduce_combine_kernel, dim3((unsigned)((S + 255) / 256)), dim3(256), 0, s, S, R, off, cap, diag,
                      (const double2*)lps, (const double*)partials, eloc, err);
 }
 

@@ -40,6 +40,8 @@ void launch_count(const HamDev& H, const uint64_t* x, long long S, int R, int gp
 // exclusive scan; tmp holds scan_tiles(n) + 1 values
 long long scan_tiles(long long n);
 void launch_scan(const int* cnt, long long n, long long* off, long long* tmp, hipStream_t s);
+// one wave per sample and range, its lanes on the range's groups (else one thread)
+bool write_by_wave(bool tables, long long max_gterms);
 void launch_write(const HamDev& H, const uint64_t* x, long long S, int R, int gper,
                   const long long* off, long long cap, uint64_t* xe, double* he, int* esample,
                   int hstride, unsigned* err, hipStream_t s);
