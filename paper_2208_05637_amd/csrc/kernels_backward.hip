@@ -106,139 +106,150 @@ void launch_pack_masked(const Geom& g, const float* params, void* wm, hipStream_
 }
 
 // ---------------------------------------------------- fused-kernel packing
-// Value of the packed operand of fragment part (layer 1 / hidden / head) at
-// sorted row `row` and packed column `k`, zero where masked or out of range.
-__device__ float packed_value(const Geom& g, const float* params, int part, int layer, int row, int k) {
-  const int n = g.n, h = g.h;
-  if (g.net_kind == 2) {         // separate phase network: dense, units in their own order
-    if (part == 0) {             // columns: the first n-2 positions
-      if (row >= h || k >= n - 2) return 0.f;
-      return params[g.poff[poff_phase_layer(g, 1)] + (long long)row * (n - 2) + k];
-    }
-    if (part == 1) {
-      if (row >= h || k >= h) return 0.f;
-      return params[g.poff[poff_phase_layer(g, layer)] + (long long)row * h + k];
-    }
-    if (row >= 4 || k >= h) return 0.f;
-    return params[g.poff[poff_phase_head(g)] + (long long)row * h + k];
-  }
-  if (part == 0) {               // layer 1: rows sorted units, cols positions
-    if (row >= h || k >= n) return 0.f;
-    const int deg = class_of_sorted(g, row) + 1;
-    if (!(k < deg)) return 0.f;
-    return params[g.poff[0] + (long long)orig_of_sorted(g, row) * n + g.order[k]];
-  }
-  if (part == 1) {               // hidden layer `layer` (2..L)
-    if (row >= h || k >= h) return 0.f;
-    const int lim = prefix_of_class(g, class_of_sorted(g, row) + 1);
-    if (!(k < lim)) return 0.f;
-    return params[g.poff[2 * (layer - 1)] + (long long)orig_of_sorted(g, row) * h + orig_of_sorted(g, k)];
-  }
-  // head: rows positions 0..n-1 then 4 phase rows
-  if (k >= h || row >= n + 4) return 0.f;
-  if (row < n) {
-    if (!(k < prefix_of_class(g, row))) return 0.f;
-    return params[g.poff[2 * g.L] + (long long)g.order[row] * h + orig_of_sorted(g, k)];
-  }
-  if (g.net_kind == 1 || !(k < prefix_of_class(g, n - 2))) return 0.f;
-  return params[g.poff[poff_phase_head(g)] + (long long)(row - n) * h + orig_of_sorted(g, k)];
+// One wave packs a fragment of TB sorted rows, each lane E consecutive columns
+// of its row; after the fragments, threads pack the biases.  A row is a stretch
+// of weights up to `lim`; sorted units are visited class by class, original
+// unit after original unit n - 1 apart, so a lane divides once for its row and
+// once for its first column.  700 fragments (44 qubits, L = 3, 512 units) are
+// less than a wave per SIMD: bound by the chain from index to load.  7 us; with
+// each element located by itself, blocks searched one by one and the biases in
+// a launch of their own 25 us.
+__device__ __forceinline__ int block_of(const int* __restrict__ off, int blocks, long long local, int lane) {
+  int blk = 0;   // the last block that starts at or before `local`
+  for (int b0 = 1; b0 <= blocks; b0 += 64)
+    blk += __popcll(__ballot(b0 + lane <= blocks && local >= off[min(b0 + lane, blocks)]));
+  return blk;
 }
 
-__global__ void pack_fused_kernel(Geom g, const float* __restrict__ params, uint4* __restrict__ out) {
-  const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long f = tid >> 6;
-  const int lane = (int)(tid & 63);
-  if (f >= g.nfrag) return;
-  int part, layer = 1, blk, ks;
-  long long local;
-  if (f < g.frag_h) {
-    part = 0;
-    local = f;
-    blk = 0;
-    while (blk + 1 <= g.NB && local >= g.off1[blk + 1]) ++blk;
-    ks = (int)(local - g.off1[blk]);
-  } else if (f < g.frag_head) {
-    part = 1;
-    const long long per = g.offh[g.NB];
-    layer = 2 + (int)((f - g.frag_h) / per);
-    local = (f - g.frag_h) % per;
-    blk = 0;
-    while (blk + 1 <= g.NB && local >= g.offh[blk + 1]) ++blk;
-    ks = (int)(local - g.offh[blk]);
-  } else {
-    part = 2;
-    local = f - g.frag_head;
-    blk = 0;
-    while (blk + 1 <= g.NHB && local >= g.offo[blk + 1]) ++blk;
-    ks = (int)(local - g.offo[blk]);
+template <int P>
+__global__ __launch_bounds__(256) void pack_fused_kernel(Geom g, const float* __restrict__ params,
+                                                         uint4* __restrict__ out, void* __restrict__ bias) {
+  constexpr bool B16 = P == P_BF16 || P == P_BF16X3 || P == P_BF16W;
+  constexpr int TB = P == P_F64 ? 16 : 32, E = B16 ? 8 : P == P_F32 ? 4 : 2, KSTEP = E * 64 / TB;
+  const int n = g.n, h = g.h;
+  const int frag_blocks = (int)((g.nfrag + 3) / 4);
+  if ((int)blockIdx.x >= frag_blocks) {
+    using S = typename std::conditional<P == P_F64, double, float>::type;
+    const long long i = (long long)(blockIdx.x - frag_blocks) * 256 + threadIdx.x;
+    const long long nh = (long long)g.L * h;
+    if (i >= nh + (long long)g.NHB * g.TB) return;
+    S v = 0;
+    if (i < nh) {
+      const int l = (int)(i / h), u = (int)(i % h);
+      v = (S)(g.net_kind == 2 ? params[g.poff[poff_phase_layer(g, l + 1) + 1] + u]
+                              : params[g.poff[2 * l + 1] + orig_of_sorted(g, u)]);
+    } else {
+      const int t = (int)(i - nh);
+      if (g.net_kind == 2) {
+        if (t < 4) v = (S)params[g.poff[poff_phase_head(g) + 1] + t];
+      } else if (t < n) {
+        v = (S)params[g.poff[2 * g.L + 1] + g.order[t]];
+      } else if (t < n + 4 && g.net_kind == 0) {
+        v = (S)params[g.poff[poff_phase_head(g) + 1] + (t - n)];
+      }
+    }
+    ((S*)bias)[i] = v;
+    return;
   }
-  uint4 hi = make_uint4(0, 0, 0, 0), lo = make_uint4(0, 0, 0, 0);
-  if (g.prec == P_BF16 || g.prec == P_BF16X3 || g.prec == P_BF16W) {
-    const int row = 32 * blk + (lane & 31);
-    const int k0 = 16 * ks + 8 * (lane >> 5);
-    unsigned short vh[8], vl[8];
+  const int lane = threadIdx.x & 63;
+  const long long f = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (f >= g.nfrag) return;
+  // the fragment's block and k step, then the lane's row: its weights, the first masked column
+  const int row_l = lane % TB, kofs = E * (lane / TB);
+  int k0, lim = 0;
+  const float* w = params;
+  enum { POSITIONS, UNITS, PLAIN } cols;
+  if (f < g.frag_h) {                    // layer 1: sorted units x positions
+    const int blk = block_of(g.off1, g.NB, f, lane), row = TB * blk + row_l;
+    k0 = KSTEP * (int)(f - g.off1[blk]) + kofs;
+    if (g.net_kind == 2) {               // (separate phase network: dense, units in their own order)
+      cols = PLAIN;
+      lim = row < h ? n - 2 : 0;
+      w += g.poff[poff_phase_layer(g, 1)] + (long long)row * (n - 2);
+    } else {
+      cols = POSITIONS;
+      if (row < h) {
+        lim = min(n, class_of_sorted(g, row) + 1);
+        w += g.poff[0] + (long long)orig_of_sorted(g, row) * n;
+      }
+    }
+  } else if (f < g.frag_head) {          // hidden layers 2..L
+    const long long per = g.offh[g.NB];
+    const int layer = 2 + (int)((f - g.frag_h) / per);
+    const long long local = (f - g.frag_h) % per;
+    const int blk = block_of(g.offh, g.NB, local, lane), row = TB * blk + row_l;
+    k0 = KSTEP * (int)(local - g.offh[blk]) + kofs;
+    if (g.net_kind == 2) {
+      cols = PLAIN;
+      lim = row < h ? h : 0;
+      w += g.poff[poff_phase_layer(g, layer)] + (long long)row * h;
+    } else {
+      cols = UNITS;
+      if (row < h) {
+        lim = min(h, prefix_of_class(g, class_of_sorted(g, row) + 1));
+        w += g.poff[2 * (layer - 1)] + (long long)orig_of_sorted(g, row) * h;
+      }
+    }
+  } else {                               // head: positions 0..n-1, then 4 phase rows
+    const long long local = f - g.frag_head;
+    const int blk = block_of(g.offo, g.NHB, local, lane), row = TB * blk + row_l;
+    k0 = KSTEP * (int)(local - g.offo[blk]) + kofs;
+    cols = g.net_kind == 2 ? PLAIN : UNITS;
+    if (g.net_kind == 2) {
+      lim = row < 4 ? h : 0;
+      w += g.poff[poff_phase_head(g)] + (long long)row * h;
+    } else if (row < n) {
+      lim = min(h, prefix_of_class(g, row));
+      w += g.poff[2 * g.L] + (long long)g.order[row] * h;
+    } else if (row < n + 4 && g.net_kind == 0) {
+      lim = min(h, prefix_of_class(g, n - 2));
+      w += g.poff[poff_phase_head(g)] + (long long)(row - n) * h;
+    }
+  }
+  float v[E];
+  int c = 0, o = k0;                     // UNITS: class and original unit of column k0
+  if (cols == UNITS) {
+    c = class_of_sorted(g, min(k0, h - 1));
+    o = c + (min(k0, h - 1) - prefix_of_class(g, c)) * (n - 1);
+  }
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    const bool in = k0 + j < lim;
+    v[j] = in ? w[cols == POSITIONS ? (int)g.order[in ? k0 + j : 0] : o] : 0.f;
+    if (cols == UNITS) {
+      const bool same = o + n - 1 < h;
+      c += same ? 0 : 1;
+      o = same ? o + n - 1 : c;
+    } else {
+      o += 1;
+    }
+  }
+  uint4 hi, lo = make_uint4(0, 0, 0, 0);
+  if constexpr (B16) {
+    unsigned vh[8], vl[8];
+#pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const float v = packed_value(g, params, part, layer, row, k0 + j);
-      vh[j] = rne_bf16(v);
-      vl[j] = rne_bf16(v - __uint_as_float(((unsigned)vh[j]) << 16));
+      vh[j] = rne_bf16(v[j]);
+      vl[j] = rne_bf16(v[j] - __uint_as_float(vh[j] << 16));
     }
     hi = make_uint4(vh[0] | (vh[1] << 16), vh[2] | (vh[3] << 16), vh[4] | (vh[5] << 16), vh[6] | (vh[7] << 16));
     lo = make_uint4(vl[0] | (vl[1] << 16), vl[2] | (vl[3] << 16), vl[4] | (vl[5] << 16), vl[6] | (vl[7] << 16));
-  } else if (g.prec == P_F32) {
-    const int row = 32 * blk + (lane & 31);
-    const int k0 = 8 * ks + 4 * (lane >> 5);
-    float v[4];
-    for (int j = 0; j < 4; ++j) v[j] = packed_value(g, params, part, layer, row, k0 + j);
+  } else if constexpr (P == P_F32) {
     hi = __builtin_bit_cast(uint4, make_float4(v[0], v[1], v[2], v[3]));
   } else {
-    const int row = 16 * blk + (lane & 15);
-    const int k0 = 8 * ks + 2 * (lane >> 4);
-    double v[2];
-    for (int j = 0; j < 2; ++j) v[j] = (double)packed_value(g, params, part, layer, row, k0 + j);
-    hi = __builtin_bit_cast(uint4, make_double2(v[0], v[1]));
+    hi = __builtin_bit_cast(uint4, make_double2((double)v[0], (double)v[1]));
   }
   out[f * 64 + lane] = hi;
   if (g.planes == 2) out[(g.nfrag + f) * 64 + lane] = lo;
 }
 
-template <typename S>
-__global__ void pack_bias_kernel(Geom g, const float* __restrict__ params, S* __restrict__ b) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long nh = (long long)g.L * g.h;
-  const long long total = nh + (long long)g.NHB * g.TB;
-  if (i >= total) return;
-  S v = 0;
-  if (g.net_kind == 2) {
-    if (i < nh) {
-      const int l = (int)(i / g.h), u = (int)(i % g.h);
-      v = (S)params[g.poff[poff_phase_layer(g, l + 1) + 1] + u];
-    } else {
-      const int t = (int)(i - nh);
-      if (t < 4) v = (S)params[g.poff[poff_phase_head(g) + 1] + t];
-    }
-  } else if (i < nh) {
-    const int l = (int)(i / g.h), u = (int)(i % g.h);
-    v = (S)params[g.poff[2 * l + 1] + orig_of_sorted(g, u)];
-  } else {
-    const int t = (int)(i - nh);
-    if (t < g.n) v = (S)params[g.poff[2 * g.L + 1] + g.order[t]];
-    else if (t < g.n + 4 && g.net_kind == 0) v = (S)params[g.poff[poff_phase_head(g) + 1] + (t - g.n)];
-  }
-  b[i] = v;
-}
-
 void launch_pack_fused(const Geom& g, const float* params, void* packed, hipStream_t s) {
-  const long long threads = g.nfrag * 64;
-  hipLaunchKernelGGL(pack_fused_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, g,
-                     params, (uint4*)packed);
   const long long nb = (long long)g.L * g.h + (long long)g.NHB * g.TB;
+  const dim3 grid((unsigned)((g.nfrag + 3) / 4 + (nb + 255) / 256)), block(256);
   void* bias = (char*)packed + g.bias_byte;
-  if (g.prec == P_F64)
-    hipLaunchKernelGGL(pack_bias_kernel<double>, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, g,
-                       params, (double*)bias);
-  else
-    hipLaunchKernelGGL(pack_bias_kernel<float>, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, g,
-                       params, (float*)bias);
+  auto kern = g.prec == P_F64 ? pack_fused_kernel<P_F64> : g.prec == P_F32 ? pack_fused_kernel<P_F32>
+                                                                           : pack_fused_kernel<P_BF16>;
+  hipLaunchKernelGGL(kern, grid, block, 0, s, g, params, (uint4*)packed, bias);
 }
 
 // ------------------------------------------------------------ small GEMM
