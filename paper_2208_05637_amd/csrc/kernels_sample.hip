@@ -282,18 +282,17 @@ __global__ void sample_finish_kernel(const uint64_t* __restrict__ x, const long 
   ow[i] = (double)cnt[i];
 }
 
-// The step's elimination and compaction in one workgroup, for buffers of up to
-// kFoldEntries entries: the same threshold, quota and order as the kernels
+// The step's elimination and compaction in one workgroup, for small buffers
+// (below kShareEntries entries): the same threshold, quota and order as the kernels
 // above.  Ten launches of a few microseconds each and 40 passes of the
 // bisection over the counts took 130 us a step at 16,384 entries (60 us at
-// 1,000); this takes 28 us (9 us): two to four passes over the counts and one
+// 1,000); this takes 30 us (8 us): two to four passes over the counts and one
 // over the children, each bound by the latency of one CU's loads.
 //
 // Threshold: the counts are binned by their magnitude and next five bits (exact
 // below 64), the bin that holds the umax-th largest count is found from the
 // top, and the remaining bits of that bin's counts are binned 11 at a time.
 constexpr int kFoldBins = 2048;
-
 __device__ __forceinline__ int fold_bin(unsigned long long v) {
   const int e = 63 - __clzll((long long)v);
   return e < 5 ? (int)v : (e - 4) * 32 + (int)((v >> (e - 5)) & 31);
@@ -453,6 +452,162 @@ __global__ __launch_bounds__(kSelThreads) void sample_fold_kernel(const uint64_t
   if (tid == 0) *d_u = nz < umax ? nz : umax;
 }
 
+// The same on many workgroups, for buffers of kShareEntries entries and more.
+// Each workgroup bins all counts and finds the bin with the umax-th largest;
+// on a second reading the counts in that bin go to a list in LDS, which is
+// binned further for the threshold, and those above it among the children
+// before its own give its place in the buffer.  That all workgroups do the same
+// costs less than passing it on (binned by the splitting kernel's lanes with
+// global atomics: 51 us more there).  16,384 entries at 60 qubits: 19 us a step
+// where one workgroup took 30 (24 qubits, 256 units, a whole call: 1.27 ms of
+// 1.73 at 40,000 entries, 0.92 of 0.91 at 4,096, 0.93 of 0.87 at 2,048).  A bin
+// of more counts than the list holds (a flat distribution) is binned from memory.
+constexpr int kShareEntries = 4096;
+constexpr int kShareList = 2048;
+
+template <int W>
+__global__ __launch_bounds__(kSelThreads) void sample_share_kernel(
+    const uint64_t* __restrict__ kx, const long long* __restrict__ kc, const long long* __restrict__ d_nk,
+    long long umax, uint64_t* __restrict__ x, long long* __restrict__ cnt, const int* __restrict__ anc_in,
+    int* __restrict__ anc_out, long long* __restrict__ d_u) {
+  constexpr int COPIES = 4;                      // of the histogram, by lane: fewer lanes meet in a bin
+  __shared__ unsigned hist[kFoldBins * COPIES];
+  __shared__ long long sh[18];
+  __shared__ int wa[kSelThreads / 64], wb[kSelThreads / 64], listed;
+  __shared__ unsigned long long lv[kShareList];
+  __shared__ int li[kShareList];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int nk = (int)*d_nk, U = nk / 2, i0 = blockIdx.x * kSelThreads;
+  if (i0 >= nk) return;
+  for (int k = tid; k < kFoldBins * COPIES; k += kSelThreads) hist[k] = 0;
+  if (tid == 0) listed = 0;
+  __syncthreads();
+  constexpr int B = 16;
+  // fn(count, child) of children [0, to), the loads of B in flight
+  auto each = [&](int to, auto fn) {
+    for (int j = tid; j < to; j += B * kSelThreads) {
+      long long v[B];
+#pragma unroll
+      for (int k = 0; k < B; ++k) v[k] = kc[min(j + k * kSelThreads, nk - 1)];
+#pragma unroll
+      for (int k = 0; k < B; ++k)
+        if (j + k * kSelThreads < to) fn((unsigned long long)v[k], j + k * kSelThreads);
+    }
+  };
+  each(nk, [&](unsigned long long v, int) {
+    if (v > 0) atomicAdd(&hist[fold_bin(v) * COPIES + lane % COPIES], 1u);
+  });
+  __syncthreads();
+  {
+    unsigned a = 0, b = 0;
+    for (int k = 0; k < COPIES; ++k) {
+      a += hist[tid * COPIES + k];
+      b += hist[(tid + kSelThreads) * COPIES + k];
+    }
+    __syncthreads();
+    hist[tid] = a;
+    hist[tid + kSelThreads] = b;
+  }
+  __syncthreads();
+  auto block_sum = [&](int v, int* part) {
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    if (lane == 0) part[wv] = v;
+    __syncthreads();
+    int tot = 0;
+    for (int k = 0; k < kSelThreads / 64; ++k) tot += part[k];
+    return tot;
+  };
+  const long long nz = block_sum((int)(hist[tid] + hist[tid + kSelThreads]), wa);
+  // counts of [lo, lo + 2^shift) straddle the threshold; without elimination lo = 0 and all counts are above
+  unsigned long long lo = 0;
+  int shift = 0, bin;
+  long long above, need = 0;
+  if (nz > umax) {
+    need = umax;
+    fold_find(hist, need, sh, bin, above);
+    need -= above;
+    shift = bin < 32 ? 0 : bin / 32 - 1;
+    lo = bin < 32 ? (unsigned long long)bin : (unsigned long long)(32 + bin % 32) << shift;
+  }
+  int gt = 0, eq = 0;                            // among the children before this workgroup's
+  const int end = shift > 0 ? nk : i0;
+  each(end, [&](unsigned long long v, int i) {
+    if (v < lo) return;
+    if (((v - lo) >> shift) != 0) {
+      gt += i < i0 ? 1 : 0;
+    } else if (shift > 0) {
+      const int at = atomicAdd(&listed, 1);
+      if (at < kShareList) {
+        lv[at] = v;
+        li[at] = i;
+      }
+    } else {
+      eq += 1;                                   // (lo > 0: exactly the threshold; lo = 0: an empty child)
+    }
+  });
+  __syncthreads();
+  const int m = listed;
+  // fn(count, child) of the bin's counts
+  auto members = [&](auto fn) {
+    if (m <= kShareList) {
+      for (int k = tid; k < m; k += kSelThreads) fn(lv[k], li[k]);
+    } else {
+      each(nk, fn);
+    }
+  };
+  const unsigned long long blo = lo;
+  const int bshift = shift;
+  while (shift > 0) {
+    const int r = shift < 11 ? shift : 11;
+    hist[tid] = 0;
+    hist[tid + kSelThreads] = 0;
+    __syncthreads();
+    members([&](unsigned long long v, int) {
+      const unsigned long long d = v - lo;
+      if (v >= lo && (d >> shift) == 0) atomicAdd(&hist[d >> (shift - r)], 1u);
+    });
+    __syncthreads();
+    fold_find(hist, need, sh, bin, above);
+    need -= above;
+    shift -= r;
+    lo += (unsigned long long)bin << shift;
+  }
+  const long long tau = (long long)lo;
+  if (bshift > 0)
+    members([&](unsigned long long v, int i) {
+      if (i < i0 && v >= blo && ((v - blo) >> bshift) == 0) {
+        gt += v > lo ? 1 : 0;
+        eq += v == lo ? 1 : 0;
+      }
+    });
+  if (tau == 0) eq = 0;
+  const int gt0 = block_sum(gt, wa), eq0 = block_sum(eq, wb), q = (int)need;
+  __syncthreads();
+  // this workgroup's children, one per thread
+  const int i = i0 + tid;
+  const long long v = i < nk ? kc[i] : 0;
+  const bool tie = tau > 0 && v == tau;
+  const unsigned long long be = __ballot(tie), below = (1ull << lane) - 1;
+  if (lane == 0) wa[wv] = __popcll(be);
+  __syncthreads();
+  int rank = eq0 + __popcll(be & below);
+  for (int k = 0; k < wv; ++k) rank += wa[k];
+  const bool keep = v > tau || (tie && rank < q);
+  const unsigned long long bk = __ballot(keep);
+  if (lane == 0) wb[wv] = __popcll(bk);
+  __syncthreads();
+  if (keep) {
+    int d = gt0 + (eq0 < q ? eq0 : q) + __popcll(bk & below);
+    for (int k = 0; k < wv; ++k) d += wb[k];
+#pragma unroll
+    for (int w = 0; w < W; ++w) x[(long long)d * W + w] = kx[(long long)i * W + w];
+    cnt[d] = v;
+    const int parent = i < U ? i : i - U;
+    if (anc_out) anc_out[d] = anc_in ? anc_in[parent] : parent;
+  }
+  if (blockIdx.x == 0 && tid == 0) *d_u = nz < umax ? nz : umax;
+}
+
 static unsigned blocks_for(long long n, int t) { return (unsigned)((n + t - 1) / t); }
 
 void launch_sample_init(uint64_t* x, int words, long long* cnt, long long n_draws, long long* d_u, hipStream_t s) {
@@ -467,7 +622,13 @@ void launch_sample_step(const SampleBufs& b, long long umax, int t, int q, uint6
   // more workgroups spread over more CUs (17 -> 15 us at 16,384 entries)
   hipLaunchKernelGGL(split, dim3(blocks_for(umax, 64)), dim3(64), 0, s, b.x, b.cnt,
                      (const double2*)b.cond, b.d_u, umax, t, q, seed, b.kx, b.kc, b.d_nk);
-  if (umax <= kFoldEntries) {
+  if (umax >= kShareEntries && umax <= kFoldEntries) {
+    auto share = b.words == 2 ? sample_share_kernel<2> : sample_share_kernel<1>;
+    hipLaunchKernelGGL(share, dim3(blocks_for(n2, kSelThreads)), dim3(kSelThreads), 0, s, b.kx, b.kc, b.d_nk, umax,
+                       b.x, b.cnt, anc_in, anc_out, b.d_u);
+    return;
+  }
+  if (umax < kShareEntries) {
     auto fold = b.words == 2 ? sample_fold_kernel<2> : sample_fold_kernel<1>;
     hipLaunchKernelGGL(fold, dim3(1), dim3(kSelThreads), 0, s, b.kx, b.kc, umax, b.x, b.cnt, anc_in, anc_out, b.d_u);
     return;
