@@ -174,43 +174,61 @@ void launch_diag(const HamDev& H, const uint64_t* x, long long S, double* diag, 
   else hipLaunchKernelGGL((diag_kernel<false, 1>), dim3(blocks), dim3(256), 0, s, H, x, S, diag);
 }
 
-// One thread per sample, one block row per range of gper groups (excluding
-// the empty flip).  Counts the valid (sample, group) pairs.
-template <bool IMAG, int W>
-__global__ void count_kernel(HamDev H, const uint64_t* __restrict__ xs, long long S, int R, int gper,
-                             int* __restrict__ cnt) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+// LN lanes per sample, one block row per range of gper groups (excluding the
+// empty flip).  Counts the valid (sample, group) pairs.  Bound by the latency of
+// the flips' loads, so eight are in flight; where samples and ranges alone leave
+// SIMDs with less than three waves, eight lanes share a range: 7 us at 16
+// qubits, 3,500 samples and ranges of 128, one lane 21; at 40 qubits and 8,192
+// samples one lane takes 206 us, eight 273.
+template <bool IMAG, int W, int LN>
+__global__ __launch_bounds__(256) void count_kernel(HamDev H, const uint64_t* __restrict__ xs, long long S, int R,
+                                                    int gper, int* __restrict__ cnt) {
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x, i = t / LN;
+  const int sub = (int)(t % LN);
   const int r = blockIdx.y;
   const int g0 = H.gfirst + r * gper;
   const int g1 = min(H.G, g0 + gper);
   const Bits<W> x = load_bits<W>(xs, i < S ? i : 0);
   int c = 0;
-  for (int g = g0; g < g1; ++g) {
-    const Bits<W> f = load_bits<W>(H.gx, g);
-    bool ok;
-    if (H.filter) {
-      ok = sector_ok<W>(x, f);
-    } else {
+  if (H.filter) {
+    constexpr int B = 8;
+    for (int g = g0 + sub; g < g1; g += B * LN) {
+      Bits<W> f[B];
+#pragma unroll
+      for (int k = 0; k < B; ++k) f[k] = load_bits<W>(H.gx, min(g + k * LN, g1 - 1));
+#pragma unroll
+      for (int k = 0; k < B; ++k) c += g + k * LN < g1 && sector_ok<W>(x, f[k]) ? 1 : 0;
+    }
+  } else {
+    for (int g = g0 + sub; g < g1; g += LN) {
       double re, im;
       group_value<IMAG, W>(H, x, g, re, im);
-      ok = (re != 0.0) || (im != 0.0);
+      c += (re != 0.0) || (im != 0.0) ? 1 : 0;
     }
-    c += ok ? 1 : 0;
   }
-  if (i < S) cnt[i * R + r] = c;
+#pragma unroll
+  for (int d = LN / 2; d >= 1; d >>= 1) c += __shfl_xor(c, d);
+  if (sub == 0 && i < S) cnt[i * R + r] = c;
+}
+
+template <int LN>
+static void launch_count_lanes(const HamDev& H, const uint64_t* x, long long S, int R, int gper, int* cnt,
+                               hipStream_t s) {
+  const dim3 grid((unsigned)((S * LN + 255) / 256), (unsigned)R), block(256);
+  if (H.words == 2) {
+    if (H.tim) hipLaunchKernelGGL((count_kernel<true, 2, LN>), grid, block, 0, s, H, x, S, R, gper, cnt);
+    else hipLaunchKernelGGL((count_kernel<false, 2, LN>), grid, block, 0, s, H, x, S, R, gper, cnt);
+    return;
+  }
+  if (H.tim) hipLaunchKernelGGL((count_kernel<true, 1, LN>), grid, block, 0, s, H, x, S, R, gper, cnt);
+  else hipLaunchKernelGGL((count_kernel<false, 1, LN>), grid, block, 0, s, H, x, S, R, gper, cnt);
 }
 
 void launch_count(const HamDev& H, const uint64_t* x, long long S, int R, int gper, int* cnt,
                   hipStream_t s) {
   if (S <= 0) return;
-  dim3 grid((unsigned)((S + 255) / 256), (unsigned)R);
-  if (H.words == 2) {
-    if (H.tim) hipLaunchKernelGGL((count_kernel<true, 2>), grid, dim3(256), 0, s, H, x, S, R, gper, cnt);
-    else hipLaunchKernelGGL((count_kernel<false, 2>), grid, dim3(256), 0, s, H, x, S, R, gper, cnt);
-    return;
-  }
-  if (H.tim) hipLaunchKernelGGL((count_kernel<true, 1>), grid, dim3(256), 0, s, H, x, S, R, gper, cnt);
-  else hipLaunchKernelGGL((count_kernel<false, 1>), grid, dim3(256), 0, s, H, x, S, R, gper, cnt);
+  if (S * R < 200000) launch_count_lanes<8>(H, x, S, R, gper, cnt, s);
+  else launch_count_lanes<1>(H, x, S, R, gper, cnt, s);
 }
 
 // Exclusive scan of n counts into off[0..n] (off[n] = total) in three

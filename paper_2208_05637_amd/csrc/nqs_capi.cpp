@@ -192,14 +192,14 @@ struct WsLayout {
   int tree_grid;       // workgroups of the prefix-shared forward the given workspace has states for
 };
 
-// Enumeration grid for chunks of S samples: R ranges of gper flip groups, of a
-// wave's width and more where the entries are written by waves (12 qubits, 256
-// samples: 14 us, with ranges of one group 33; 16 qubits, 3,500 samples: 53 us,
-// with ranges of 13 groups 195).
+// Enumeration grid for chunks of S samples: R ranges of gper flip groups, of
+// 128 and more where the entries are written by waves, whose lanes take the
+// groups a sample keeps of a range (16 qubits, 3,500 samples: 40 us, with ranges
+// of 64 groups 53, of 13 groups 195; 76 qubits, 250 samples: 173, 366 and 590).
 static void grid_for(const nqs_ham* h, int64_t S, int ngroups, int& R, int& gper) {
   const int bx = (int)((S + 255) / 256);
   if (ngroups <= 0) { R = 1; gper = 0; return; }
-  const int most = write_by_wave(h->tables, h->max_gterms) ? ngroups / 64 : ngroups;
+  const int most = write_by_wave(h->tables, h->max_gterms) ? ngroups / 128 : ngroups;
   const int r = std::max(1, std::min(most, 2048 / bx));
   gper = (ngroups + r - 1) / r;
   R = (ngroups + gper - 1) / gper;
