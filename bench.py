@@ -55,13 +55,29 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def kernel_source_hash():
+def kernel_source_hash(kernel="fused_forward"):
     import hashlib
     h = hashlib.sha256()
-    for f in ("paper_2208_05637_amd/csrc/kernels_forward.hip", "paper_2208_05637_amd/csrc/net.h"):
+    source = {"fused_forward": "kernels_forward.hip", "tree_forward": "kernels_tree.hip"}[kernel]
+    for f in (f"paper_2208_05637_amd/csrc/{source}", "paper_2208_05637_amd/csrc/net.h"):
         with open(os.path.join(ROOT, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
+
+
+def tree_traffic(workload, prec):
+    """HBM bytes per configuration of the prefix-shared forward (its states
+    included) from its committed counter summary, or None as below."""
+    path = os.path.join(ROOT, "profiles", f"tree_forward_{workload}_{prec}_traffic.md")
+    if not os.path.exists(path):
+        return None
+    with open(path) as fh:
+        text = fh.read()
+    if kernel_source_hash("tree_forward") not in text:
+        return None
+    import re
+    m = re.search(r"traffic_bytes_per_row:\s*`?([0-9.]+)", text)
+    return float(m.group(1)) if m else None
 
 
 def measured_traffic(workload, prec, waves, rows):
@@ -457,7 +473,12 @@ def main():
         f"{achieved:.1f} TFLOP/s algorithmic, {issued:.1f} TFLOP/s MFMA issued (peak {peak})")
     el_main = eloc.cpu().numpy()
     E_main = energy.cpu().numpy()
-    bpr = measured_traffic(args.workload, prec, kinfo["waves_per_block"], kinfo["rows_per_block"])
+    # down the prefix tree fewer products are issued than the network has row by row: the rate of
+    # those that are issued is the kernel's, and the row-by-row work over the same time goes beside it
+    shared = prof["forward_flops_executed"] < prof["forward_flops"]
+    bpr = (tree_traffic(args.workload, prec) if shared
+           else measured_traffic(args.workload, prec, kinfo["waves_per_block"], kinfo["rows_per_block"]))
+    rate = issued if shared else achieved
     out = {
         "metric": METRIC,
         "value": value,
@@ -497,12 +518,13 @@ def main():
             "forward_rows_per_step": prof["forward_rows"] / steps,
         },
         "roofline": {
-            "kernel": f"fused_forward<{prec},{cfg['h']}>",
+            "kernel": f"{'tree' if shared else 'fused'}_forward<{prec},{cfg['h']}>",
             "bound": "mfma",
-            "achieved": achieved,
+            "achieved": rate,
             "peak": peak,
             "unit": "TFLOP/s",
-            "frac": achieved / peak,
+            "frac": rate / peak,
+            "row_by_row_equivalent_tflops": achieved,
             # HBM bytes per launch: the counters' bytes per configuration times this run's
             # configurations per launch
             "traffic": (None if bpr is None else bpr * prof["forward_rows"] / max(prof["forward_launches"], 1)),

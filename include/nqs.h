@@ -247,7 +247,7 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
                            int64_t max_batch, uint32_t flags, int64_t chunk_samples,
                            nqs_plan** out);
 /* Bytes a call on batch samples can use.  The last part holds the prefix states
-   of the connected-configuration forward (up to two workgroups per CU): calls
+   of the connected-configuration forward (two workgroups per CU): calls
    also take a workspace without all of it, and evaluate the same values with
    fewer workgroups, or row by row. */
 nqs_status nqs_plan_workspace_size(const nqs_plan* plan, int64_t batch, size_t* bytes);

@@ -27,13 +27,14 @@
 // A workgroup of eight waves walks its own segment of rows depth first, a tile
 // of M nodes at a time, and keeps two tiles of states per level, so states need
 // room per workgroup and not for every node of the call.  Two workgroups share
-// a CU and fill each other's barriers; at 60 qubits and 1024 units a tile of
-// the last level holds the matrix cores for 9,200 of its 25,000 cycles, the
-// rest being state traffic (3.2 TB/s of reads and writes past L2), the
-// conversions of the activations and the short phases around the layers.
-// Measured on 146 million rows (2,000 samples) at 60 qubits, L = 4, 1024 units:
-// 193 ms against 610 ms row by row; 117 million rows at 40 qubits, L = 3, 512
-// units: 27 ms against 88 ms.
+// a CU and fill each other's barriers (one alone takes 1.26 times as long).  At
+// 60 qubits and 1024 units the matrix cores are busy 35% of the time, beside
+// state traffic of 3.2 TB/s past L2; at 64 qubits and 512 units 20%, where the
+// vector instructions of the conversions and the log-sigmoids take half of the
+// issue cycles and the activations' reads most of LDS's rate during the products.
+// Measured on 2,000 samples at 60 qubits, L = 4, 1024 units: 191 ms against
+// 610 ms row by row; 8,192 samples at 40 qubits, L = 3, 512 units: 32 ms against
+// 88 ms; 400 samples (38 million rows) at 64 qubits: 27.6 ms against 63 ms.
 #include <algorithm>
 #include <atomic>
 
