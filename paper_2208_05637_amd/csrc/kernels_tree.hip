@@ -64,6 +64,15 @@ template <> struct Kind<P_BF16W>  { static constexpr int TB = 32, KSTEP = 16, PL
 template <> struct Kind<P_F32>    { static constexpr int TB = 32, KSTEP = 8, PL = 1, PLW = 1, RB = 1, SLOTS = 4; using Acc = f32x16; using S = float; };
 template <> struct Kind<P_F64>    { static constexpr int TB = 16, KSTEP = 8, PL = 1, PLW = 1, RB = 1, SLOTS = 5; using Acc = f64x4; using S = double; };
 
+// A tile of MB row blocks: two, whose row blocks share a wave's weight
+// fragments, or one, where whole tiles would leave CUs without one (the
+// sampler's smaller buffers).
+template <int P, int MB> struct Shape {
+  static constexpr int M = MB * Kind<P>::TB;
+  static constexpr int RB = MB == 2 ? Kind<P>::RB : 1;
+  static constexpr int SLOTS = MB == 2 ? Kind<P>::SLOTS : P == P_F64 ? 3 : 2;
+};
+
 // One product of a weight and an activation fragment; AX: the activations are
 // exact in BF16 (the +-1 inputs), their low plane is zero.
 template <int P, bool AX>
@@ -128,10 +137,9 @@ __device__ __forceinline__ void lds_barrier() {
 // activation fragments of a product are read while the one before it is
 // multiplied (the barriers keep that order: left alone, the compiler reads each
 // right before its MFMA and every MFMA waits for LDS).
-template <int P, bool AX, class ActFn>
-__device__ __forceinline__ void strip(typename Kind<P>::Acc (&acc)[Kind<P>::RB], const Weights& wb, int base, int mb,
+template <int P, int RB, bool AX, class ActFn>
+__device__ __forceinline__ void strip(typename Kind<P>::Acc (&acc)[RB], const Weights& wb, int base, int mb,
                                       int k0, int kend, ActFn act) {
-  constexpr int RB = Kind<P>::RB;
   uint4 wa[Kind<P>::PLW], wc[Kind<P>::PLW], f0[Kind<P>::PL], f1[Kind<P>::PL];
   auto step = [&](uint4 (&w)[Kind<P>::PLW], int k, uint4 (&f)[Kind<P>::PL], uint4 (&g)[Kind<P>::PL]) {
     if constexpr (RB == 2) {
@@ -191,7 +199,7 @@ __device__ __forceinline__ uint4 input_frag(const uint64_t* y, int mb, int ks, i
 
 // relu(acc + bias) of local block lb, row block mb into the activations, in
 // the operand order of the next layer (plane: bytes to the low plane).
-template <int P>
+template <int P, int MB>
 __device__ __forceinline__ void store_act(char* act, const typename Kind<P>::Acc& acc,
                                           const typename Kind<P>::S* bias, int lb, int mb, int lane, int plane) {
   using T = Kind<P>;
@@ -203,7 +211,7 @@ __device__ __forceinline__ void store_act(char* act, const typename Kind<P>::Acc
       double t = acc[rr] + bias[16 * lb + nl];
       t = t > 0.0 ? t : 0.0;
       const int kk = nl & 7;
-      *(double*)(act + (((2 * lb + (nl >> 3)) * 2 + mb) * 64 + m + 16 * (kk >> 1)) * 16 + 8 * (kk & 1)) = t;
+      *(double*)(act + (((2 * lb + (nl >> 3)) * MB + mb) * 64 + m + 16 * (kk >> 1)) * 16 + 8 * (kk & 1)) = t;
     }
   } else {
 #pragma unroll
@@ -213,9 +221,9 @@ __device__ __forceinline__ void store_act(char* act, const typename Kind<P>::Acc
       float v2 = acc[4 * q + 2] + b4.z, v3 = acc[4 * q + 3] + b4.w;
       v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f);
       if constexpr (P == P_F32) {
-        *(float4*)(act + (((4 * lb + q) * 2 + mb) * 64 + m + 32 * g) * 16) = make_float4(v0, v1, v2, v3);
+        *(float4*)(act + (((4 * lb + q) * MB + mb) * 64 + m + 32 * g) * 16) = make_float4(v0, v1, v2, v3);
       } else {
-        char* dst = act + (((2 * lb + (q >> 1)) * 2 + mb) * 64 + m + 32 * (q & 1)) * 16 + 8 * g;
+        char* dst = act + (((2 * lb + (q >> 1)) * MB + mb) * 64 + m + 32 * (q & 1)) * 16 + 8 * g;
         const unsigned h01 = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){v0, v1}, bf16x2));
         const unsigned h23 = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){v2, v3}, bf16x2));
         *(uint2*)dst = make_uint2(h01, h23);
@@ -296,10 +304,10 @@ __host__ __device__ inline long long state_units(const Geom& g, int cb) {
 }
 
 // LDS of a tile of M nodes.
-template <int P, int W>
+template <int P, int W, int MB>
 struct TileLds {
   using S = typename Kind<P>::S;
-  static constexpr int M = 2 * Kind<P>::TB;
+  static constexpr int M = Shape<P, MB>::M;
   char* act;           // activations of the level's own units, by k fragment and row block
   int plane;           // bytes to their low plane
   S* stage;            // [M][stage_ld] head outputs
@@ -310,7 +318,7 @@ struct TileLds {
   int* pidx;           // the nodes' parents: places in the parents' state
   __device__ TileLds(void* smem, int own_max, int ld) {
     act = (char*)smem;
-    plane = own_max * (Kind<P>::TB / Kind<P>::KSTEP) * 2 * 1024;
+    plane = own_max * (Kind<P>::TB / Kind<P>::KSTEP) * MB * 1024;
     stage = (S*)(act + Kind<P>::PL * plane);
     stage_ld = ld;
     blds = stage + M * ld;
@@ -345,22 +353,22 @@ struct TileJob {
   int place;
 };
 
-template <int P, int W>
-__device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W>& t, Weights wb,
+template <int P, int W, int MB>
+__device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W, MB>& t, Weights wb,
                                            const typename Kind<P>::S* biases, int ksplit, int wv, const TileJob& jb) {
   using T = Kind<P>;
   using Acc = typename T::Acc;
   using S = typename T::S;
-  constexpr int TB = T::TB, KB = TB / T::KSTEP, PL = T::PL, RB = T::RB, SLOTS = T::SLOTS;
+  constexpr int TB = T::TB, KB = TB / T::KSTEP, PL = T::PL, RB = Shape<P, MB>::RB, SLOTS = Shape<P, MB>::SLOTS;
   const int tid = thread_index(), lane = tid & 63, col = lane % TB;
   wb.voff = lane * 16;
   const int L = g.L, NB = g.NB, ca = jb.ca, cb = jb.cb, eb = jb.eb;
   const int ka = ca * KB, own = eb - ca;
-  const int node0 = ca > 0 ? t.pidx[col] : 0, node1 = ca > 0 ? t.pidx[TB + col] : 0;
+  const int node0 = ca > 0 ? t.pidx[col] : 0, node1 = MB == 2 && ca > 0 ? t.pidx[TB + col] : 0;
   const int pun = (NB - ca) * TB, sun = (NB - cb) * TB;        // units per layer in the parents' state and in this one
   char* act = t.act;
   auto lds_act = [&](int mb, int ks, uint4 (&f)[PL]) {
-    const char* a = act + (((ks - ka) * 2 + mb) * 64 + lane) * 16;
+    const char* a = act + (((ks - ka) * MB + mb) * 64 + lane) * 16;
     f[0] = *(const uint4*)a;
     if constexpr (PL == 2) f[1] = *(const uint4*)(a + t.plane);
   };
@@ -379,16 +387,16 @@ __device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W>& t
   const int wd = blockIdx.x >= gridDim.x / 2 ? wv ^ 3 : wv;
   auto own_block = [&](int s, int& mb) {
     const int r = (s & 1) ? kWaves * (s + 1) - 1 - wd : kWaves * s + (wd < 4 ? wd : 11 - wd);
-    mb = RB == 2 ? 0 : r & 1;
-    return eb - 1 - r * RB / 2;
+    mb = RB == MB ? 0 : r & 1;
+    return eb - 1 - r * RB / MB;
   };
 
   if (tid < jb.r1 - jb.r0) t.hbl[tid] = biases[(long long)L * g.h + jb.r0 + tid];
   // the input fragments, in LDS for layer 1
   if (own > 0) {
     const int kin = g.ks1[eb - 1];
-    for (int it = wv; it < 2 * kin; it += kWaves)
-      *(uint4*)(act + (it * 64 + lane) * 16) = input_frag<P, W>(t.ylds, it & 1, it >> 1, lane);
+    for (int it = wv; it < MB * kin; it += kWaves)
+      *(uint4*)(act + (it * 64 + lane) * 16) = input_frag<P, W>(t.ylds, it % MB, it / MB, lane);
   }
   lds_barrier();
   for (int l = 1; own > 0 && l <= L; ++l) {
@@ -403,17 +411,17 @@ __device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W>& t
 #pragma unroll
         for (int i = 0; i < RB; ++i) acc[s][i] = Acc{};
         if (b >= ca)
-          strip<P, true>(acc[s], wb, g.off1[b] * 1024, mb, 0, g.ks1[b], [&](int rb, int ks, uint4 (&f)[PL]) {
-            f[0] = *(const uint4*)(act + ((ks * 2 + rb) * 64 + lane) * 16);
+          strip<P, RB, true>(acc[s], wb, g.off1[b] * 1024, mb, 0, g.ks1[b], [&](int rb, int ks, uint4 (&f)[PL]) {
+            f[0] = *(const uint4*)(act + ((ks * MB + rb) * 64 + lane) * 16);
           });
       }
     } else {
       // later units' chains over these units, into the state
       if (jb.out) {
-        for (int it = wv; it < (NB - cb) * 2 / RB; it += kWaves) {
-          const int b = cb + it * RB / 2, mb = RB == 2 ? 0 : it & 1;
+        for (int it = wv; it < (NB - cb) * MB / RB; it += kWaves) {
+          const int b = cb + it * RB / MB, mb = RB == MB ? 0 : it & 1;
           parent(acc[0], l, b, mb);
-          strip<P, false>(acc[0], wb, (lbase + g.offh[b]) * 1024, mb, ka, cb * KB, lds_act);
+          strip<P, RB, false>(acc[0], wb, (lbase + g.offh[b]) * 1024, mb, ka, cb * KB, lds_act);
 #pragma unroll
           for (int i = 0; i < RB; ++i)
             state_store<P>(acc[0][i], jb.st, jb.sn, (l - 2) * sun + (b - cb) * TB, jb.place + (mb + i) * TB + col, lane);
@@ -426,7 +434,7 @@ __device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W>& t
         const int b = own_block(s, mb);
         if (b >= ca) {
           parent(acc[s], l, b, mb);
-          strip<P, false>(acc[s], wb, (lbase + g.offh[b]) * 1024, mb, ka, min(g.ksh[b], eb * KB), lds_act);
+          strip<P, RB, false>(acc[s], wb, (lbase + g.offh[b]) * 1024, mb, ka, min(g.ksh[b], eb * KB), lds_act);
         }
       }
     }
@@ -438,7 +446,7 @@ __device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W>& t
       const int b = own_block(s, mb);
       if (b >= ca) {
 #pragma unroll
-        for (int i = 0; i < RB; ++i) store_act<P>(act, acc[s][i], t.blds, b - ca, mb + i, lane, t.plane);
+        for (int i = 0; i < RB; ++i) store_act<P, MB>(act, acc[s][i], t.blds, b - ca, mb + i, lane, t.plane);
       }
     }
     lds_barrier();
@@ -446,8 +454,8 @@ __device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W>& t
 
   // head: items of one head block and one row block
   const int hun = (L - 1) * sun, phun = (L - 1) * pun;
-  for (int item = wv; item < 2 * g.NHB; item += kWaves) {
-    const int nb = item >> 1, mb = item & 1;
+  for (int item = wv; item < MB * g.NHB; item += kWaves) {
+    const int nb = item / MB, mb = item % MB;
     if (!jb.out && (TB * (nb + 1) <= jb.r0 || TB * nb >= jb.r1)) continue;   // no row wanted
     const int kso = g.kso[nb];
     const int chunk = (((kso + ksplit - 1) / ksplit) + 7) & ~7;
@@ -529,7 +537,7 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
   using S = typename Kind<P>::S;
   constexpr int M = 2 * Kind<P>::TB;
   extern __shared__ uint4 smem[];
-  const TileLds<P, W> t(smem, ta.own_max, ta.stage_ld);
+  const TileLds<P, W, 2> t(smem, ta.own_max, ta.stage_ld);
   int* cur = t.pidx + M, *pb = cur + 4, *tiles = cur + 8;      // the walk's cursors, per level
   int* nxt = cur + 12, *wcnt = cur + 16;                       // first row past the tile; wave counts
 
@@ -562,7 +570,7 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
     const bool leaf = j == ta.nlev - 1;
     const char* pst = j > 0 ? scratch + ta.lev[j - 1].st : nullptr;
     char* st = scratch + lv.st;
-    tile_units<P, W>(g, t, wb, biases, ta.ksplit, wv,
+    tile_units<P, W, 2>(g, t, wb, biases, ta.ksplit, wv,
                      TileJob{lv.ca, lv.cb, lv.eb, lv.ta, leaf ? (g.net_kind == 1 ? n : n + 4) : lv.tb, !leaf, pst,
                              2 * M, st, 2 * M, half});
 
@@ -756,13 +764,13 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
 // cond[i] = (logit at t, forcing code).  Once the level's positions are drawn,
 // a step with t < 0 writes the states of the next level.  Row by row every
 // step evaluated the whole network: 94 us a step at 60 qubits, 1024 units and
-// 16,384 entries; now 26 us, the three steps that write states among them.
-template <int P, int W>
+// 16,384 entries; now 24 us, the three steps that write states among them.
+template <int P, int W, int MB>
 __global__ __launch_bounds__(kThreads, 4) void sample_units(Geom g, StepArgs sa) {
   using S = typename Kind<P>::S;
-  constexpr int M = 2 * Kind<P>::TB;
+  constexpr int M = Shape<P, MB>::M;
   extern __shared__ uint4 smem[];
-  const TileLds<P, W> t(smem, sa.own_max, 1);
+  const TileLds<P, W, MB> t(smem, sa.own_max, 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const S* biases = (const S*)((const char*)sa.packed + g.bias_byte);
   const Weights wb = weights(g, sa.packed);
@@ -776,7 +784,7 @@ __global__ __launch_bounds__(kThreads, 4) void sample_units(Geom g, StepArgs sa)
       t.pidx[tid] = sa.ca == 0 ? 0 : sa.anc ? sa.anc[row] : (int)row;
     }
     lds_barrier();
-    tile_units<P, W>(g, t, wb, biases, sa.ksplit, wv,
+    tile_units<P, W, MB>(g, t, wb, biases, sa.ksplit, wv,
                      TileJob{sa.ca, sa.cb, sa.eb, sa.t < 0 ? 0 : sa.t, sa.t < 0 ? 0 : sa.t + 1, sa.t < 0, sa.pst,
                              sa.nodes, sa.st, sa.nodes, (int)r0});
     if (sa.t >= 0 && tid < M && r0 + tid < rows) {
@@ -883,15 +891,27 @@ void launch_w(const Geom& g, const TreePlan& t, const TreeArgs& a, int grid, hip
   hipLaunchKernelGGL((tree_forward<P, W>), dim3((unsigned)grid), dim3(kThreads), t.lds, s, g, a);
 }
 
+template <int P, int W, int MB>
+void launch_step_w(const Geom& g, const TreePlan& t, const StepArgs& a, int grid, hipStream_t s) {
+  static std::atomic<unsigned long long> done{0};
+  lds_opt_in(sample_units<P, W, MB>, done);
+  hipLaunchKernelGGL((sample_units<P, W, MB>), dim3((unsigned)grid), dim3(kThreads), t.lds, s, g, a);
+}
+
+// Tiles of one row block up to as many entries as tiles of two would give each
+// CU one of: 23.8 us a step at 60 qubits, 1024 units and 16,384 entries, in whole
+// tiles 25.5; at 24 qubits, 256 units, FP32 and 1,000 entries 9.6, 10.9.
 template <int P>
-void launch_step(const Geom& g, const TreePlan& t, const StepArgs& a, int grid, hipStream_t s) {
-  static std::atomic<unsigned long long> one{0}, two{0};
-  if (g.words == 2) {
-    lds_opt_in(sample_units<P, 2>, two);
-    hipLaunchKernelGGL((sample_units<P, 2>), dim3((unsigned)grid), dim3(kThreads), t.lds, s, g, a);
+void launch_step(const Geom& g, const TreePlan& t, const StepArgs& a, int cus, hipStream_t s) {
+  const bool half = a.umax <= (long long)t.rows * cus;
+  const long long rows = half ? t.rows / 2 : t.rows;
+  const int grid = (int)std::min<long long>((a.umax + rows - 1) / rows, 2LL * cus);
+  if (half) {
+    if (g.words == 2) launch_step_w<P, 2, 1>(g, t, a, grid, s);
+    else launch_step_w<P, 1, 1>(g, t, a, grid, s);
   } else {
-    lds_opt_in(sample_units<P, 1>, one);
-    hipLaunchKernelGGL((sample_units<P, 1>), dim3((unsigned)grid), dim3(kThreads), t.lds, s, g, a);
+    if (g.words == 2) launch_step_w<P, 2, 2>(g, t, a, grid, s);
+    else launch_step_w<P, 1, 2>(g, t, a, grid, s);
   }
 }
 
@@ -905,13 +925,13 @@ size_t sample_state_bytes(const Geom& g, int cb, long long entries) {
 void launch_sample_units(const Geom& g, const TreePlan& t, const StepArgs& sa, int cu_count, hipStream_t s) {
   StepArgs a = sa;
   a.own_max = t.args.own_max;
-  const int grid = (int)std::min<long long>((a.umax + t.rows - 1) / t.rows, 2LL * std::max(cu_count, 1));
+  const int cus = std::max(cu_count, 1);
   switch (g.prec) {
-    case P_BF16: return launch_step<P_BF16>(g, t, a, grid, s);
-    case P_BF16X3: return launch_step<P_BF16X3>(g, t, a, grid, s);
-    case P_BF16W: return launch_step<P_BF16W>(g, t, a, grid, s);
-    case P_F32: return launch_step<P_F32>(g, t, a, grid, s);
-    case P_F64: return launch_step<P_F64>(g, t, a, grid, s);
+    case P_BF16: return launch_step<P_BF16>(g, t, a, cus, s);
+    case P_BF16X3: return launch_step<P_BF16X3>(g, t, a, cus, s);
+    case P_BF16W: return launch_step<P_BF16W>(g, t, a, cus, s);
+    case P_F32: return launch_step<P_F32>(g, t, a, cus, s);
+    case P_F64: return launch_step<P_F64>(g, t, a, cus, s);
   }
 }
 

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
 
 # (n, n_up, n_dn, draws, buffer, std of the parameters): no elimination; a threshold
 # found by one bin (small counts, many ties); by the listed counts of a bin; the
-# smallest buffer; equal weights, where one bin holds more counts than the list
+# smallest buffer; equal weights, where one bin holds more counts than the list;
+# the conditionals in half and in whole tiles
 @pytest.mark.parametrize("n,nu,nd,draws,umax,std", [
     (12, 3, 3, 10**9, 4500, 0.5), (13, -1, -1, 20000, 4500, 0.1), (13, -1, -1, 10**12, 4096, 0.5),
-    (13, -1, -1, 10**12, 4500, 0.0), (14, -1, -1, 10**7, 4097, 0.3), (13, -1, -1, 3 * 10**5, 5000, 0.0)])
+    (13, -1, -1, 10**12, 4500, 0.0), (14, -1, -1, 10**7, 4097, 0.3), (13, -1, -1, 3 * 10**5, 5000, 0.0),
+    (14, -1, -1, 10**9, 8192, 0.3), (14, -1, -1, 10**9, 8193, 0.3)])
 def test_shared_elimination_matches_oracle(n, nu, nd, draws, umax, std):
     import paper_2208_05637_amd as nqs
     nqs.load()
