@@ -395,7 +395,8 @@ __global__ void write_kernel(HamDev H, const uint64_t* __restrict__ xs, long lon
 // NS = 64 samples share a staged batch; 16 where workgroups of 64 would leave
 // CUs without one.
 constexpr int kWsWaves = 4;                 // waves per workgroup
-constexpr int kWsGroups = 448;              // groups per staged batch (four workgroups per CU in LDS)
+constexpr int kWsGroups = 256;              // groups per staged batch (four workgroups per CU in LDS)
+constexpr int kWsShort = 8;                 // terms of a group that is evaluated with its neighbours
 constexpr int kWsTerms = 2048;              // terms per staged batch (and the largest group it takes)
 
 template <bool IMAG, int W, int NS>
@@ -408,7 +409,8 @@ __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
   __shared__ uint64_t ltz[kWsTerms * W];
   __shared__ double lre[kWsTerms];
   __shared__ double lim[IMAG ? kWsTerms : 1];
-  __shared__ int lkept[kWsWaves][128];   // per wave: kept groups awaiting evaluation
+  __shared__ int lkept[kWsWaves][128];   // per wave: kept groups of the sample awaiting evaluation
+  __shared__ int llong[kWsWaves][64], lplace[kWsWaves][64];   // and the long ones of all its samples
   __shared__ int lge;
   constexpr int SPW = NS / kWsWaves;   // samples per wave
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -420,7 +422,60 @@ __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
   const bool live_l = lane < SPW && i_l < S;
   Bits<W> x_l = load_bits<W>(xs, live_l ? i_l : 0);
   long long pos_l = live_l ? off[i_l * R + r] : 0;
+  const long long base = (long long)((unsigned long long)(unsigned)__builtin_amdgcn_readlane((unsigned)((unsigned long long)pos_l >> 32), 0) << 32 |
+                                     (unsigned)__builtin_amdgcn_readlane((unsigned)pos_l, 0));
   bool over = false;
+  // h_g(x) of the group at batch index q, summed over its terms in order
+  auto group_sum = [&](const Bits<W>& x, int q, double& a, double& b) {
+    a = 0.0;
+    b = 0.0;
+    const int k1 = loff[q + 1];
+    for (int kk = loff[q]; kk < k1; ++kk) {
+      int c = 0;
+#pragma unroll
+      for (int k = 0; k < W; ++k) c += __popcll(x.w[k] & ltz[kk * W + k]);
+      const unsigned long long par = (unsigned long long)(c & 1) << 63;
+      a += __longlong_as_double(__double_as_longlong(lre[kk]) ^ par);
+      if constexpr (IMAG) b += __longlong_as_double(__double_as_longlong(lim[kk]) ^ par);
+    }
+  };
+  auto store = [&](long long p, long long i, const Bits<W>& x, const Bits<W>& f, double a, double b) {
+    if (p < cap) {
+#pragma unroll
+      for (int k = 0; k < W; ++k) xe[p * W + k] = x.w[k] ^ f.w[k];
+      he[p * hstride] = a;
+      if (hstride == 2) he[p * 2 + 1] = b;
+      if (esample) esample[p] = (int)i;
+    } else {
+      over = true;
+    }
+  };
+  auto flip = [&](int q) {
+    Bits<W> f;
+#pragma unroll
+    for (int k = 0; k < W; ++k) f.w[k] = lgx[q * W + k];
+    return f;
+  };
+  // A wave runs as many terms as its longest group.  Double excitations have up
+  // to eight, single ones about one per qubit, one in 25 of the kept groups at
+  // 24 qubits but one in nearly every 64: those wait, with their samples and
+  // places, until there are enough of them or the batch ends.  114 million
+  // entries at 40 qubits: 1.41 ms, all groups together 2.35; 14.9 million at 24
+  // qubits 0.24, 0.39; 250 samples at 76 qubits 0.10, 0.17.
+  int nlong = 0;
+  auto evaluate_long = [&]() {
+    const int e = lane < nlong ? llong[wv][lane] : 0, j = e >> 16, q = e & 0xFFFF;
+    Bits<W> x;
+#pragma unroll
+    for (int k = 0; k < W; ++k) x.w[k] = __shfl((unsigned long long)x_l.w[k], j);
+    if (lane < nlong) {
+      double a, b;
+      group_sum(x, q, a, b);
+      store(base + lplace[wv][lane], (long long)blockIdx.x * NS + wv * SPW + j, x, flip(q), a, b);
+    }
+    nlong = 0;
+    __builtin_amdgcn_wave_barrier();
+  };
   for (int gb = g0; gb < g1;) {
     // the batch: groups [gb, ge) whose terms fit (a group alone always fits: the host checks)
     __syncthreads();
@@ -462,48 +517,19 @@ __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
         const unsigned hi32 = __builtin_amdgcn_readlane((unsigned)((unsigned long long)pos_l >> 32), j);
         pos = (long long)(((unsigned long long)hi32 << 32) | lo32);
       }
-      // h_g(x) of the group at batch index q, summed over its terms in order
-      auto group_sum = [&](int q, double& a, double& b) {
-        a = 0.0;
-        b = 0.0;
-        const int k1 = loff[q + 1];
-        for (int kk = loff[q]; kk < k1; ++kk) {
-          int c = 0;
-#pragma unroll
-          for (int k = 0; k < W; ++k) c += __popcll(x.w[k] & ltz[kk * W + k]);
-          const unsigned long long par = (unsigned long long)(c & 1) << 63;
-          a += __longlong_as_double(__double_as_longlong(lre[kk]) ^ par);
-          if constexpr (IMAG) b += __longlong_as_double(__double_as_longlong(lim[kk]) ^ par);
-        }
-      };
-      auto store = [&](long long p, const Bits<W>& f, double a, double b) {
-        if (p < cap) {
-#pragma unroll
-          for (int k = 0; k < W; ++k) xe[p * W + k] = x.w[k] ^ f.w[k];
-          he[p * hstride] = a;
-          if (hstride == 2) he[p * 2 + 1] = b;
-          if (esample) esample[p] = (int)i;
-        } else {
-          over = true;
-        }
-      };
       if (H.filter) {
         // the sector test decides which groups the sample keeps; they are listed
         // in order and evaluated 64 at a time, one per lane, so no lane idles on
         // a group the sample does not keep
         int* kept = lkept[wv];
-        int nk = 0;
+        int nk = 0, all = 0;
         auto evaluate = [&](int cnt) {
           if (lane < cnt) {
-            const int q = kept[lane];
-            Bits<W> f;
-#pragma unroll
-            for (int k = 0; k < W; ++k) f.w[k] = lgx[q * W + k];
+            const int e = kept[lane], q = e & 0xFFFF;
             double a, b;
-            group_sum(q, a, b);
-            store(pos + lane, f, a, b);
+            group_sum(x, q, a, b);
+            store(pos + (e >> 16), i, x, flip(q), a, b);
           }
-          pos += cnt;
         };
         for (int q0 = 0; q0 < ng; q0 += 64) {
           const int q = q0 + lane;
@@ -512,9 +538,21 @@ __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
 #pragma unroll
           for (int k = 0; k < W; ++k) f.w[k] = act ? lgx[q * W + k] : 0;
           const bool ok = act && sector_ok<W>(x, f);
-          const unsigned long long bal = __ballot(ok);
-          if (ok) kept[nk + __popcll(bal & ((1ull << lane) - 1))] = q;
-          nk += __popcll(bal);
+          const bool lg = ok && loff[q + 1] - loff[q] > kWsShort;
+          const unsigned long long bal = __ballot(ok), bl = __ballot(lg), bs = bal & ~bl, below = (1ull << lane) - 1;
+          const int rank = all + __popcll(bal & below);
+          if (ok && !lg) kept[nk + __popcll(bs & below)] = rank << 16 | q;
+          if (bl) {
+            if (nlong + __popcll(bl) > 64) evaluate_long();
+            if (lg) {
+              const int d = nlong + __popcll(bl & below);
+              llong[wv][d] = j << 16 | q;
+              lplace[wv][d] = (int)(pos - base) + rank;
+            }
+            nlong += __popcll(bl);
+          }
+          nk += __popcll(bs);
+          all += __popcll(bal);
           __builtin_amdgcn_wave_barrier();
           if (nk >= 64) {
             evaluate(64);
@@ -525,6 +563,7 @@ __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
           }
         }
         if (nk > 0) evaluate(nk);
+        pos += all;
         __builtin_amdgcn_wave_barrier();
       } else {
         // without the sector test a group is kept where h != 0: every group is evaluated
@@ -535,15 +574,16 @@ __global__ __launch_bounds__(64 * kWsWaves) void write_staged_kernel(
 #pragma unroll
           for (int k = 0; k < W; ++k) f.w[k] = act ? lgx[q * W + k] : 0;
           double a = 0.0, b = 0.0;
-          if (act) group_sum(q, a, b);
+          if (act) group_sum(x, q, a, b);
           const bool ok = act && ((a != 0.0) || (b != 0.0));
           const unsigned long long bal = __ballot(ok);
-          if (ok) store(pos + __popcll(bal & ((1ull << lane) - 1)), f, a, b);
+          if (ok) store(pos + __popcll(bal & ((1ull << lane) - 1)), i, x, f, a, b);
           pos += __popcll(bal);
         }
       }
       if (lane == j) pos_l = pos;
     }
+    if (nlong > 0) evaluate_long();
     gb = ge;
   }
   if (over) atomicOr(err, kErrEntryOverflow);

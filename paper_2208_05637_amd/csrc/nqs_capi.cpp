@@ -195,7 +195,8 @@ struct WsLayout {
 // Enumeration grid for chunks of S samples: R ranges of gper flip groups, of
 // 128 and more where the entries are written by waves, whose lanes take the
 // groups a sample keeps of a range (16 qubits, 3,500 samples: 40 us, with ranges
-// of 64 groups 53, of 13 groups 195; 76 qubits, 250 samples: 173, 366 and 590).
+// of 64 groups 53, of 13 groups 195; 76 qubits, 250 samples: 173, 366 and 590,
+// all before long groups waited for each other).
 static void grid_for(const nqs_ham* h, int64_t S, int ngroups, int& R, int& gper) {
   const int bx = (int)((S + 255) / 256);
   if (ngroups <= 0) { R = 1; gper = 0; return; }

@@ -75,3 +75,43 @@ def test_entries_diagonal_and_sum(nqs, n, terms, flips, B):
     want = np.longdouble(np.stack([size * np.cos(d[..., 1]), size * np.sin(d[..., 1])], -1)).sum(1)
     want[:, 0] += diag
     assert (np.abs(got - want) <= bar[:, None]).all()
+
+
+@pytest.mark.parametrize("n,B,every", [(12, 3, 1), (24, 70, 2), (24, 700, 1), (66, 40, 3)])
+def test_groups_of_few_and_many_terms(nqs, n, B, every):
+    """Flips within a spin, of one to eight terms or (every `every`-th) of nine
+    to thirty, which a wave collects over its samples.  Coefficients are
+    multiples of 2^-10, so that every sum is exact."""
+    print(f"enumeration: n={n} samples={B}, long groups every {every}", flush=True)
+    rng = np.random.default_rng(n + B)
+    word = lambda: sum(int(rng.integers(0, 2**32)) << (32 * k) for k in range(4)) & ((1 << n) - 1)
+    fl = sorted((1 << a) | (1 << b) for a in range(n) for b in range(a + 2, n, 2))
+    xm, zm, cf, terms = [], [], [], []
+    for k, f in enumerate(fl):
+        count = int(rng.integers(9, 31)) if k % every == 0 else int(rng.integers(1, 9))
+        zs = set()
+        while len(zs) < count:
+            zs.add(word() & ~f)
+        c = rng.integers(1, 4096, size=count) * rng.choice([-1, 1], size=count) / 1024.0
+        terms.append(list(zip(sorted(zs), c)))
+        xm += [f] * count
+        zm += sorted(zs)
+        cf += list(c)
+    ctx = nqs.Context(0)
+    H = nqs.Hamiltonian(n, _words(xm, n), _words(zm, n), np.array(cf), drop_tol=0.0, conserves_spin=True).upload(ctx)
+    nu, nd = n // 4, n // 6
+    plan = nqs.Plan(ctx, H, 1, 64, nu, nd, "fp64", max_batch=B)
+    x = [sum(1 << int(q) for q in 2 * rng.permutation(n // 2)[:nu]) +
+         sum(1 << int(q) for q in 2 * rng.permutation(n // 2)[:nd] + 1) for _ in range(B)]
+    con = nqs.connected(plan, torch.from_numpy(_words(x, n).view(np.int64)).cuda())
+    m = int(con["n_entries"].item())
+    assert nqs.device_status(plan) == 0
+    wx, wh = [], []
+    for v in x:
+        for f, ts in zip(fl, terms):
+            if bin(v & f).count("1") == 1:                                      # moves one particle
+                wx.append(v ^ f)
+                wh.append(sum(-c if bin(v & z).count("1") & 1 else c for z, c in ts))
+    assert m == len(wx)
+    np.testing.assert_array_equal(con["x"][:m].cpu().numpy().view(np.uint64), _words(wx, n))
+    np.testing.assert_array_equal(con["h"][:m, 0].cpu().numpy(), np.array(wh))
