@@ -248,9 +248,10 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
                            nqs_plan** out);
 /* Bytes a call on batch samples can use.  The last part holds the prefix states
    of the connected-configuration forward (two workgroups per CU): calls
-   also take a workspace without all of it, and evaluate the same values with
-   fewer workgroups, or row by row. */
+   also take a workspace without all of it, down to nqs_plan_workspace_least
+   bytes, and evaluate the same values with fewer workgroups, or row by row. */
 nqs_status nqs_plan_workspace_size(const nqs_plan* plan, int64_t batch, size_t* bytes);
+nqs_status nqs_plan_workspace_least(const nqs_plan* plan, int64_t batch, size_t* bytes);
 /* Plan facts: per-sample entry bound, chunk size, dedup on/off, number of
    parameters. */
 nqs_status nqs_plan_info(const nqs_plan* plan, int64_t* entries_per_sample,
@@ -399,8 +400,11 @@ typedef struct {
 /* Instances of more than 64 qubits, and instances whose forward variant
    takes the half tile (nqs_plan_configure), run their forwards as launches
    of their own inside the same call: the shared work lists take one-word
-   strings in full tiles. */
+   strings in full tiles.  The prefix states stand behind all instances' parts;
+   a workspace without all of them, down to nqs_multi_workspace_least bytes, is
+   taken as by nqs_energy_grad. */
 nqs_status nqs_multi_workspace_size(int n_inst, const nqs_instance* inst, size_t* bytes);
+nqs_status nqs_multi_workspace_least(int n_inst, const nqs_instance* inst, size_t* bytes);
 nqs_status nqs_energy_grad_multi(int n_inst, const nqs_instance* inst, void* d_ws, size_t ws_bytes);
 
 /* ---------------------------------------------------------------- sampler
@@ -423,8 +427,12 @@ nqs_status nqs_energy_grad_multi(int n_inst, const nqs_instance* inst, void* d_w
  * their draw counts as f64 weights, d_n_unique[0] = U <= max_unique, for
  * u < U in buffer order.  d_x and d_w hold max_unique entries.  The network
  * arithmetic is the plan's precision.  d_ws: nqs_sample_workspace_size
- * bytes, 256-byte aligned.  Stream-ordered, no host synchronisation. */
+ * bytes, 256-byte aligned, the entries' prefix states among them; with less,
+ * down to nqs_sample_workspace_least bytes, every position evaluates the whole
+ * network and the draws are the same.  Stream-ordered, no host
+ * synchronisation. */
 nqs_status nqs_sample_workspace_size(const nqs_plan* plan, int64_t max_unique, size_t* bytes);
+nqs_status nqs_sample_workspace_least(const nqs_plan* plan, int64_t max_unique, size_t* bytes);
 nqs_status nqs_sample(nqs_plan* plan, const float* d_params, int64_t n_draws, uint64_t seed,
                       int64_t max_unique, uint64_t* d_x, double* d_w, int64_t* d_n_unique,
                       void* d_ws, size_t ws_bytes);

@@ -81,6 +81,7 @@ SIGNATURES = {
     "nqs_net_param_count": (C.c_int, [C.POINTER(NetDesc), C.POINTER(_I64)]),
     "nqs_plan_create": (C.c_int, [_P, _P, C.POINTER(NetDesc), _I64, C.c_uint32, _I64, C.POINTER(_P)]),
     "nqs_plan_workspace_size": (C.c_int, [_P, _I64, C.POINTER(_SZ)]),
+    "nqs_plan_workspace_least": (C.c_int, [_P, _I64, C.POINTER(_SZ)]),
     "nqs_plan_info": (C.c_int, [_P, C.POINTER(_I64), C.POINTER(_I64), C.POINTER(C.c_int),
                                 C.POINTER(_I64)]),
     "nqs_plan_destroy": (None, [_P]),
@@ -95,8 +96,10 @@ SIGNATURES = {
     "nqs_energy_grad": (C.c_int, [_P, _P, _P, _P, _I64, _P, _P, _P, _P, _SZ]),
     "nqs_energy_grad_noalloc": (C.c_int, [_P, _P, _P, _P, _I64, _P, _P, _P, _P]),
     "nqs_multi_workspace_size": (C.c_int, [C.c_int, C.POINTER(Instance), C.POINTER(_SZ)]),
+    "nqs_multi_workspace_least": (C.c_int, [C.c_int, C.POINTER(Instance), C.POINTER(_SZ)]),
     "nqs_energy_grad_multi": (C.c_int, [C.c_int, C.POINTER(Instance), _P, _SZ]),
     "nqs_sample_workspace_size": (C.c_int, [_P, _I64, C.POINTER(_SZ)]),
+    "nqs_sample_workspace_least": (C.c_int, [_P, _I64, C.POINTER(_SZ)]),
     "nqs_sample": (C.c_int, [_P, _P, _I64, C.c_uint64, _I64, _P, _P, _P, _P, _SZ]),
     "nqs_connected": (C.c_int, [_P, _P, _I64, _I64, _P, _P, _P, _P, _P, _P, _P, _P, _P, _SZ]),
     "nqs_reduce_table": (C.c_int, [_P, _I64, _P, _P, _P, _P, _P, _I64, _P, _P, _SZ]),

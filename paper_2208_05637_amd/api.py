@@ -202,6 +202,7 @@ class Plan:
         self.handle = h
         self.max_batch = int(max_batch)
         self._ws = None
+        self._least = False
         self._refresh()
 
     def _refresh(self):
@@ -246,17 +247,26 @@ class Plan:
         return dict(candidates=cands, chosen=rep.chosen, from_cache=bool(rep.from_cache),
                     probe_samples=rep.probe_samples)
 
-    def workspace_size(self, B):
+    def workspace_size(self, B, least=False):
+        """Bytes that a call on B samples can use; least: bytes it cannot do without."""
         out = C.c_size_t()
-        L.check(self.lib.nqs_plan_workspace_size(self.handle, int(B), C.byref(out)),
-                "nqs_plan_workspace_size")
+        name = "nqs_plan_workspace_least" if least else "nqs_plan_workspace_size"
+        L.check(getattr(self.lib, name)(self.handle, int(B), C.byref(out)), name)
         return out.value
 
-    def workspace(self, B=None):
-        """A cached device workspace large enough for batch B (default: max_batch)."""
-        need = self.workspace_size(self.max_batch if B is None else B)
+    def workspace(self, B=None, least=None):
+        """A cached device workspace large enough for batch B (default: max_batch).
+        least=True allocates and keeps to no more than the calls need (least=False:
+        again what they can use); without either, a plan falls back to it where
+        the device has no room for more."""
+        if least is not None and least != self._least:
+            self._ws, self._least = None, least
+        B = self.max_batch if B is None else B
+        need = self.workspace_size(B, self._least)
         if self._ws is None or self._ws[1] < need:
-            raw = torch.empty(need + 256, dtype=torch.uint8, device=self.ctx.device)
+            self._ws = None
+            raw, need, fell_back = _workspace(need, lambda: self.workspace_size(B, True), self.ctx.device)
+            self._least |= fell_back
             aligned = (raw.data_ptr() + 255) & ~255
             self._ws = (raw, need, aligned)
         return C.c_void_p(self._ws[2]), self._ws[1]
@@ -275,6 +285,18 @@ class Plan:
         if getattr(self, "handle", None):
             self.lib.nqs_plan_destroy(self.handle)
             self.handle = None
+
+
+def _workspace(need, least, device):
+    """(raw tensor, bytes, whether they are the least): `need` bytes with room to align them, or least() where the
+    device has no room for that."""
+    try:
+        return torch.empty(need + 256, dtype=torch.uint8, device=device), need, False
+    except torch.OutOfMemoryError:
+        few = least()
+        if few >= need:
+            raise
+    return torch.empty(few + 256, dtype=torch.uint8, device=device), few, True
 
 
 def _dev_tensor(t, name, dtypes, numel, device):
@@ -386,8 +408,14 @@ def multi_workspace(items):
     lib = L.load()
     need = C.c_size_t()
     L.check(lib.nqs_multi_workspace_size(len(items), _instances(items), C.byref(need)), "nqs_multi_workspace_size")
-    raw = torch.empty(need.value + 256, dtype=torch.uint8, device=items[0]["plan"].ctx.device)
-    return raw, C.c_void_p((raw.data_ptr() + 255) & ~255), need.value
+
+    def least():
+        few = C.c_size_t()
+        L.check(lib.nqs_multi_workspace_least(len(items), _instances(items), C.byref(few)), "nqs_multi_workspace_least")
+        return few.value
+
+    raw, nb, _ = _workspace(need.value, least, items[0]["plan"].ctx.device)
+    return raw, C.c_void_p((raw.data_ptr() + 255) & ~255), nb
 
 
 def energy_grad_multi(items, workspace=None):
@@ -418,14 +446,21 @@ def sample(plan, params, n_draws, seed, max_unique):
     need = C.c_size_t()
     L.check(plan.lib.nqs_sample_workspace_size(plan.handle, int(max_unique), C.byref(need)),
             "nqs_sample_workspace_size")
-    raw = torch.empty(need.value + 256, dtype=torch.uint8, device=dev)
+
+    def least():
+        few = C.c_size_t()
+        L.check(plan.lib.nqs_sample_workspace_least(plan.handle, int(max_unique), C.byref(few)),
+                "nqs_sample_workspace_least")
+        return few.value
+
+    raw, nb, _ = _workspace(need.value, least, dev)
     ws = C.c_void_p((raw.data_ptr() + 255) & ~255)
     x = torch.empty(int(max_unique) if plan.words == 1 else (int(max_unique), plan.words), dtype=torch.int64,
                     device=dev)
     w = torch.empty(int(max_unique), dtype=torch.float64, device=dev)
     nu = torch.zeros(1, dtype=torch.int64, device=dev)
     L.check(plan.lib.nqs_sample(plan.handle, _ptr(params), int(n_draws), int(seed) & (2**64 - 1),
-                                int(max_unique), _ptr(x), _ptr(w), _ptr(nu), ws, need.value), "nqs_sample")
+                                int(max_unique), _ptr(x), _ptr(w), _ptr(nu), ws, nb), "nqs_sample")
     U = int(nu.item())
     return x[:U], w[:U]
 

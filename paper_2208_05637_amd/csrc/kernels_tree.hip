@@ -754,7 +754,7 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
     }
   }
   if (ta.prof_slot && threadIdx.x == 0)
-    atomicAdd((unsigned long long*)ta.prof_slot + kProfSlots, (unsigned long long)issued);
+    atomicAdd((unsigned long long*)ta.issued, (unsigned long long)issued);
 }
 
 // One step of the sampler's walk: every entry of the buffer is a node whose
@@ -958,7 +958,7 @@ int tree_head_ksplit(const Geom& g, int waves, int rows) {
 
 void launch_tree_forward(const Geom& g, const TreePlan& t, int ksplit, const void* packed, const uint64_t* x,
                          long long rows_bound, const long long* d_count, double* out, long long* prof_slot,
-                         void* scratch, int grid, hipStream_t s) {
+                         long long* issued, void* scratch, int grid, hipStream_t s) {
   if (rows_bound <= 0 || grid <= 0) return;
   TreeArgs a = t.args;
   a.packed = packed;
@@ -967,6 +967,7 @@ void launch_tree_forward(const Geom& g, const TreePlan& t, int ksplit, const voi
   a.bound = rows_bound;
   a.out = out;
   a.prof_slot = prof_slot;
+  a.issued = issued;
   a.scratch = (char*)scratch;
   a.ksplit = ksplit;
   grid = (int)std::min<long long>(grid, (rows_bound + t.rows - 1) / t.rows);

@@ -179,16 +179,21 @@ struct nqs_plan {
   double flops_alg_row = 0, flops_exec_row = 0;   // forward flops per configuration
   double flops_exec_phase_row = 0;                // of the second, the separate phase network's
   // profiling
-  struct Rec { hipEvent_t a, b; int kind; int slot; };   // kind 0 call, 1 eloc, 2 forward
+  // kind 0 call, 1 eloc, 2 forward; issued: place of a prefix-shared forward's flops in the workspace, else 0
+  struct Rec { hipEvent_t a, b; int kind; int slot; size_t issued; };
   bool prof = false;
   std::vector<Rec> recs;
   int next_slot = 0;
 };
 
+constexpr int kProfSlots = 8192;   // profiled launches between two reads
+
 struct WsLayout {
   size_t err, prof, geom, packed, wm, lps, eloc, energy, cnt, off, stmp, rpart, diag, xe, he, lpe, htab,
       eu, xu, nu, dfirst, drank, drtmp, htab2, lp2, lpn, src, nnew, bscratch, total;
-  size_t tree, full;   // the prefix tree's states come last: total is what a call needs, full what it can use
+  // the prefix tree's part comes last (the MFMA flops of profiled launches, the
+  // workgroups' states): total is what a call needs, full what it can use
+  size_t issued, tree, full;
   int tree_grid;       // workgroups of the prefix-shared forward the given workspace has states for
 };
 
@@ -212,7 +217,7 @@ static WsLayout layout(const nqs_plan* p, int64_t B) {
   auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
   const int hs = p->ham->has_imag ? 2 : 1;
   L.err = take(256);
-  L.prof = take((size_t)2 * kProfSlots * 8);   // row counts, then the prefix-shared forwards' MFMA flops
+  L.prof = take((size_t)kProfSlots * 8);
   L.geom = take(2 * sizeof(Geom));
   L.packed = take(p->packed_bytes);
   L.wm = take((size_t)p->g.n_params * p->bw);
@@ -245,9 +250,11 @@ static WsLayout layout(const nqs_plan* p, int64_t B) {
   }
   L.bscratch = take((size_t)backward_scratch_elems(p->g, p->Sb) * p->bw);
   L.total = o;
-  L.tree = o;
+  L.issued = L.tree = o;
   L.tree_grid = 0;
   if (p->tree) {
+    L.issued = take((size_t)kProfSlots * 8);
+    L.tree = o;
     // two workgroups per CU, and no more than the chunk has smallest segments
     L.tree_grid = (int)std::min<int64_t>(2 * std::max(p->ctx->cu_count, 1), (p->EC + p->tp.rows - 1) / p->tp.rows);
     take((size_t)L.tree_grid * p->tp.args.scratch_wg);
@@ -268,12 +275,13 @@ static bool tree_pays(const nqs_plan* p, int64_t most_rows) {
   return p->levels && waves * (8e-6 + rows * p->flops_exec_row / rate) > 100e-6;
 }
 
-// A workspace of `bytes` (at least total) may hold states for fewer
+// With `room` bytes for the tree's part there may be states for fewer
 // workgroups; below an eighth of the CUs the row-by-row forward is faster.
-static void fit_tree(const nqs_plan* p, size_t bytes, WsLayout& L) {
-  if (!L.tree_grid || bytes >= L.full) return;
-  const int fits = (int)((bytes - L.tree) / (size_t)p->tp.args.scratch_wg);
-  L.tree_grid = fits >= std::min(L.tree_grid, p->ctx->cu_count / 8) ? fits : 0;
+static void fit_tree(const nqs_plan* p, size_t room, WsLayout& L) {
+  if (!L.tree_grid || room >= L.full - L.total) return;
+  const size_t slots = L.tree - L.issued;
+  const int fits = room > slots ? (int)((room - slots) / (size_t)p->tp.args.scratch_wg) : 0;
+  L.tree_grid = fits >= std::max(1, std::min(L.tree_grid, p->ctx->cu_count / 8)) ? fits : 0;
 }
 
 // group 0 is the empty flip
@@ -886,17 +894,19 @@ nqs_status nqs_plan_profile_read(nqs_plan* p, void* ws, nqs_profile* out) {
   if (!p || !out) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
   memset(out, 0, sizeof(*out));
   HIP_TRY(hipStreamSynchronize(p->ctx->stream));
-  std::vector<long long> slots, issued;
+  std::vector<long long> slots;
   if (p->next_slot > 0) {
     if (!ws) return fail(NQS_ERR_INVALID_ARGUMENT, "workspace is NULL");
     WsLayout L = layout(p, 0);
     slots.resize(std::min(p->next_slot, kProfSlots));
-    issued.resize(slots.size());
     HIP_TRY(hipMemcpy(slots.data(), (char*)ws + L.prof, slots.size() * 8, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(issued.data(), (char*)ws + L.prof + (size_t)kProfSlots * 8, slots.size() * 8,
-                      hipMemcpyDeviceToHost));
   }
-  for (auto& r : p->recs) {
+  std::vector<long long> issued(p->recs.size(), 0);
+  for (size_t k = 0; k < p->recs.size(); ++k)
+    if (p->recs[k].issued)
+      HIP_TRY(hipMemcpy(&issued[k], (char*)ws + p->recs[k].issued, 8, hipMemcpyDeviceToHost));
+  for (size_t k = 0; k < p->recs.size(); ++k) {
+    const nqs_plan::Rec& r = p->recs[k];
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, r.a, r.b));
     if (r.kind == 0) { out->calls += 1; out->call_ms += ms; }
@@ -909,8 +919,8 @@ nqs_status nqs_plan_profile_read(nqs_plan* p, void* ws, nqs_profile* out) {
         const double rows = (double)slots[r.slot];
         out->forward_rows += rows;
         // a separate phase network's rows run row by row beside the modulus network's tree
-        const double plain = rows * (issued[r.slot] ? p->flops_exec_phase_row : p->flops_exec_row);
-        out->forward_flops_executed += (double)issued[r.slot] + plain;
+        const double plain = rows * (r.issued ? p->flops_exec_phase_row : p->flops_exec_row);
+        out->forward_flops_executed += (double)issued[k] + plain;
       }
     }
   }
@@ -929,6 +939,13 @@ nqs_status nqs_plan_workspace_size(const nqs_plan* p, int64_t B, size_t* bytes) 
   if (!p || !bytes) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
   if (B < 0 || B > p->max_batch) return fail(NQS_ERR_INVALID_ARGUMENT, "batch %lld outside 0..%lld", (long long)B, (long long)p->max_batch);
   *bytes = layout(p, B).full;
+  return NQS_OK;
+}
+
+nqs_status nqs_plan_workspace_least(const nqs_plan* p, int64_t B, size_t* bytes) {
+  if (!p || !bytes) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
+  if (B < 0 || B > p->max_batch) return fail(NQS_ERR_INVALID_ARGUMENT, "batch %lld outside 0..%lld", (long long)B, (long long)p->max_batch);
+  *bytes = layout(p, B).total;
   return NQS_OK;
 }
 
@@ -952,7 +969,7 @@ static nqs_status check_ws(const nqs_plan* p, int64_t B, void* ws, size_t ws_byt
   if (B < 0 || B > p->max_batch) return fail(NQS_ERR_INVALID_ARGUMENT, "batch %lld outside 0..%lld", (long long)B, (long long)p->max_batch);
   L = layout(p, B);
   if (ws_bytes < L.total) return fail(NQS_ERR_WORKSPACE_TOO_SMALL, "workspace %zu < %zu bytes", ws_bytes, L.total);
-  fit_tree(p, ws_bytes, L);
+  fit_tree(p, ws_bytes - L.total, L);
   return NQS_OK;
 }
 
@@ -967,10 +984,10 @@ static hipEvent_t prof_mark(nqs_plan* p) {
   (void)hipEventRecord(e, p->ctx->stream);
   return e;
 }
-static void prof_close(nqs_plan* p, hipEvent_t a, int kind, int slot) {
+static void prof_close(nqs_plan* p, hipEvent_t a, int kind, int slot, size_t issued = 0) {
   if (!p->prof || !a) return;
   hipEvent_t b = prof_mark(p);
-  if (b) p->recs.push_back({a, b, kind, slot});
+  if (b) p->recs.push_back({a, b, kind, slot, issued});
 }
 
 // Packed weights of the plan's network(s) into the packed region.
@@ -990,18 +1007,17 @@ static void forward_net(const nqs_plan* p, const void* packed, const uint64_t* x
                    out, nullptr, s);
 }
 
-// The same of connected configurations in the enumeration's order: down their
-// prefix tree where the plan has one and the workspace its states.
-static void forward_connected(const nqs_plan* p, void* ws, const WsLayout& L, const void* packed, const uint64_t* x,
-                              long long bound, const long long* d_count, double* out, long long* slot,
-                              hipStream_t s) {
-  if (!L.tree_grid || !tree_pays(p, bound)) {
-    forward_net(p, packed, x, bound, d_count, out, slot, s);
-    return;
-  }
+// Whether rows of connected configurations (their bound) go down the prefix tree.
+static bool by_tree(const nqs_plan* p, const WsLayout& L, long long bound) { return L.tree_grid && tree_pays(p, bound); }
+
+// The same of connected configurations in the enumeration's order, down their
+// prefix tree.
+static void forward_tree(const nqs_plan* p, void* ws, const WsLayout& L, const void* packed, const uint64_t* x,
+                         long long bound, const long long* d_count, double* out, long long* slot, long long* issued,
+                         hipStream_t s) {
   const int waves = forward_variant_waves(p->g.prec, p->g.h, p->variant);
   const int rows = forward_variant_rows(p->g.prec, p->g.h, p->variant);
-  launch_tree_forward(p->g, p->tp, tree_head_ksplit(p->g, waves, rows), packed, x, bound, d_count, out, slot,
+  launch_tree_forward(p->g, p->tp, tree_head_ksplit(p->g, waves, rows), packed, x, bound, d_count, out, slot, issued,
                       at<void>(ws, L.tree), L.tree_grid, s);
   if (p->two)
     launch_forward(p->gp, p->variant, p->resident, p->ctx->cu_count, (const char*)packed + p->packed_phase, x, bound,
@@ -1012,17 +1028,22 @@ static void forward_profiled(nqs_plan* p, void* ws, const WsLayout& L, const voi
                              const uint64_t* x, long long bound, const long long* d_count, double* out,
                              bool connected) {
   hipEvent_t a = prof_mark(p);
+  const bool tree = connected && by_tree(p, L, bound);
   long long* slot = nullptr;
+  long long* issued = nullptr;
   int si = -1;
   if (p->prof && p->next_slot < kProfSlots) {
     si = p->next_slot++;
     slot = at<long long>(ws, L.prof) + si;
     launch_fill_u64(slot, 0ull, 1, p->ctx->stream);   // a launch with no tiles leaves it at zero rows
-    launch_fill_u64(slot + kProfSlots, 0ull, 1, p->ctx->stream);
+    if (tree) {
+      issued = at<long long>(ws, L.issued) + si;
+      launch_fill_u64(issued, 0ull, 1, p->ctx->stream);
+    }
   }
-  if (connected) forward_connected(p, ws, L, packed, x, bound, d_count, out, slot, p->ctx->stream);
+  if (tree) forward_tree(p, ws, L, packed, x, bound, d_count, out, slot, issued, p->ctx->stream);
   else forward_net(p, packed, x, bound, d_count, out, slot, p->ctx->stream);
-  prof_close(p, a, 2, si);
+  prof_close(p, a, 2, si, issued ? (size_t)((char*)issued - (char*)ws) : 0);
 }
 
 // The connected configurations of one chunk, ready for the forward.
@@ -1196,12 +1217,12 @@ nqs_status nqs_energy_grad(nqs_plan* p, const float* params, const uint64_t* x, 
   if (st != NQS_OK) return st;
   if (t0) {
     hipEvent_t t1 = prof_mark(p);
-    if (t1) p->recs.push_back({t0, t1, 1, -1});
+    if (t1) p->recs.push_back({t0, t1, 1, -1, 0});
   }
   energy_and_grad(p, params, x, w, B, el, energy, grad, ws, L);
   if (t0) {
     hipEvent_t t2 = prof_mark(p);
-    if (t2) p->recs.push_back({t0, t2, 0, -1});
+    if (t2) p->recs.push_back({t0, t2, 0, -1, 0});
   }
   return launch_check("energy gradient");
 }
@@ -1238,11 +1259,14 @@ nqs_status nqs_energy_grad_noalloc(nqs_plan* p, const float* params, const uint6
   return st;
 }
 
-// Workspace of a multi-instance call: each instance's layout, 256-byte aligned, in order.
-static nqs_status multi_layout(int n_inst, const nqs_instance* inst, std::vector<size_t>& base, size_t& total) {
+// Workspace of a multi-instance call: each instance's layout up to its tree's
+// part, 256-byte aligned, in order (base), up to `total`; then the trees' parts
+// in order, up to `full`.
+static nqs_status multi_layout(int n_inst, const nqs_instance* inst, std::vector<size_t>& base, size_t& total,
+                               size_t& full) {
   if (n_inst < 0 || (n_inst > 0 && !inst)) return fail(NQS_ERR_INVALID_ARGUMENT, "bad instance list");
   base.assign(n_inst, 0);
-  total = 0;
+  total = full = 0;
   for (int i = 0; i < n_inst; ++i) {
     const nqs_instance& I = inst[i];
     if (!I.plan) return fail(NQS_ERR_INVALID_ARGUMENT, "instance %d has no plan", i);
@@ -1250,22 +1274,33 @@ static nqs_status multi_layout(int n_inst, const nqs_instance* inst, std::vector
     if (I.B < 1 || I.B > I.plan->max_batch)
       return fail(NQS_ERR_INVALID_ARGUMENT, "instance %d: batch %lld outside 1..%lld", i, (long long)I.B,
                   (long long)I.plan->max_batch);
+    const WsLayout L = layout(I.plan, I.B);
     base[i] = total;
-    total += align256(layout(I.plan, I.B).full);
+    total += align256(L.total);
+    full += L.full - L.total;
   }
+  full += total;
   return NQS_OK;
 }
 
 nqs_status nqs_multi_workspace_size(int n_inst, const nqs_instance* inst, size_t* bytes) {
   if (!bytes) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
   std::vector<size_t> base;
-  return multi_layout(n_inst, inst, base, *bytes);
+  size_t total = 0;
+  return multi_layout(n_inst, inst, base, total, *bytes);
+}
+
+nqs_status nqs_multi_workspace_least(int n_inst, const nqs_instance* inst, size_t* bytes) {
+  if (!bytes) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
+  std::vector<size_t> base;
+  size_t full = 0;
+  return multi_layout(n_inst, inst, base, *bytes, full);
 }
 
 nqs_status nqs_energy_grad_multi(int n_inst, const nqs_instance* inst, void* ws, size_t ws_bytes) {
   std::vector<size_t> base;
-  size_t total = 0;
-  nqs_status st = multi_layout(n_inst, inst, base, total);
+  size_t total = 0, full = 0;
+  nqs_status st = multi_layout(n_inst, inst, base, total, full);
   if (st != NQS_OK) return st;
   if (n_inst == 0) return NQS_OK;
   if (!ws) return fail(NQS_ERR_INVALID_ARGUMENT, "workspace is NULL");
@@ -1282,10 +1317,16 @@ nqs_status nqs_energy_grad_multi(int n_inst, const nqs_instance* inst, void* ws,
   std::vector<WsLayout> L(n_inst);
   std::vector<void*> W(n_inst);
   std::vector<double*> EL(n_inst);
+  size_t tail = total;   // the trees' parts, of what lies behind the layouts: each its own, the last what is left
   for (int i = 0; i < n_inst; ++i) {
     nqs_plan* p = inst[i].plan;
     W[i] = (char*)ws + base[i];
     L[i] = layout(p, inst[i].B);
+    const size_t room = std::min(L[i].full - L[i].total, ws_bytes - tail), move = tail - (base[i] + L[i].total);
+    fit_tree(p, room, L[i]);
+    L[i].issued += move;
+    L[i].tree += move;
+    tail += room;
     EL[i] = inst[i].d_eloc ? inst[i].d_eloc : at<double>(W[i], L[i].eloc);
     launch_fill_u32(at<void>(W[i], L[i].err), 0u, 1, s);
     launch_store_geom(p->g, at<Geom>(W[i], L[i].geom), s);
@@ -1370,8 +1411,9 @@ nqs_status nqs_energy_grad_multi(int n_inst, const nqs_instance* inst, void* ws,
       c0s.push_back(c0);
       scs.push_back(Sc);
       cfs.push_back(cf);
-      if (L[i].tree_grid && tree_pays(p, cf.bound))
-        forward_connected(p, W[i], L[i], at<void>(W[i], L[i].packed), cf.x, cf.bound, cf.d_count, cf.out, nullptr, s);
+      if (by_tree(p, L[i], cf.bound))
+        forward_tree(p, W[i], L[i], at<void>(W[i], L[i].packed), cf.x, cf.bound, cf.d_count, cf.out, nullptr, nullptr,
+                     s);
       else
         add_segs(i, cf.x, cf.d_count, cf.out, cf.bound, ids, segs);
     }
@@ -1388,7 +1430,7 @@ nqs_status nqs_energy_grad_multi(int n_inst, const nqs_instance* inst, void* ws,
   }
   if (t0) {
     hipEvent_t t1 = prof_mark(p0);
-    if (t1) p0->recs.push_back({t0, t1, 0, -1});
+    if (t1) p0->recs.push_back({t0, t1, 0, -1, 0});
   }
   return launch_check("energy gradient (multi)");
 }
@@ -1695,6 +1737,14 @@ nqs_status nqs_sample_workspace_size(const nqs_plan* p, int64_t max_unique, size
   return NQS_OK;
 }
 
+nqs_status nqs_sample_workspace_least(const nqs_plan* p, int64_t max_unique, size_t* bytes) {
+  if (!p || !bytes) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
+  if (max_unique < 1 || max_unique > (1LL << 30))
+    return fail(NQS_ERR_INVALID_ARGUMENT, "max_unique %lld outside 1..2^30", (long long)max_unique);
+  *bytes = sample_layout(p, max_unique).total;
+  return NQS_OK;
+}
+
 nqs_status nqs_sample(nqs_plan* p, const float* params, int64_t n_draws, uint64_t seed, int64_t max_unique,
                       uint64_t* d_x, double* d_w, int64_t* d_n_unique, void* ws, size_t ws_bytes) {
   if (!p || !params || !d_x || !d_w || !d_n_unique) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
@@ -1877,8 +1927,8 @@ nqs_status nqs_device_status(nqs_ctx* ctx, void* ws, uint32_t* flags) {
 nqs_status nqs_multi_device_status(int n_inst, const nqs_instance* inst, void* ws, uint32_t* flags) {
   if (!ws || !flags) return fail(NQS_ERR_INVALID_ARGUMENT, "NULL argument");
   std::vector<size_t> base;
-  size_t total = 0;
-  nqs_status st = multi_layout(n_inst, inst, base, total);
+  size_t total = 0, full = 0;
+  nqs_status st = multi_layout(n_inst, inst, base, total, full);
   if (st != NQS_OK) return st;
   *flags = 0;
   if (n_inst == 0) return NQS_OK;

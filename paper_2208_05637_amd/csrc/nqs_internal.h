@@ -108,7 +108,6 @@ void launch_energy(const double* eloc, const double* w, long long B, double* ene
 // log-sigmoids of positions [ta, tb) are complete.  The last level's nodes are
 // the rows.
 constexpr int kTreeLevels = 4;
-constexpr int kProfSlots = 8192;   // profiled launches between two reads
 struct TreeLevel {
   int ca, cb, eb, d, ta, tb;
   long long st;
@@ -120,7 +119,8 @@ struct TreeArgs {
   const long long* d_count;   // nullable: then rows = bound
   long long bound;
   double* out;
-  long long* prof_slot;       // nullable: receives the row count, and kProfSlots further on the MFMA flops
+  long long* prof_slot;       // nullable: receives the row count
+  long long* issued;          // with prof_slot: receives the MFMA flops on top
   char* scratch;              // scratch_wg bytes per workgroup
   long long scratch_wg;
   int nlev, ksplit, own_max, stage_ld;
@@ -141,7 +141,7 @@ int tree_head_ksplit(const Geom& g, int waves, int rows);
 // of x, equal to launch_forward's logits with that shape's head slices.
 void launch_tree_forward(const Geom& g, const TreePlan& t, int ksplit, const void* packed, const uint64_t* x,
                          long long rows_bound, const long long* d_count, double* out, long long* prof_slot,
-                         void* scratch, int grid, hipStream_t s);
+                         long long* issued, void* scratch, int grid, hipStream_t s);
 
 // One step of the sampler's walk over its entries (kernels_tree.hip): units of
 // blocks [ca, eb) from the states pst of the units before ca; t >= 0: cond[i] =
