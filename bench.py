@@ -317,6 +317,8 @@ def main():
     ap.add_argument("--waves", type=int, default=0, help="force the forward's waves per workgroup")
     ap.add_argument("--resident", type=int, default=None, choices=[0, 1],
                     help="with --waves: force the forward's grid (1 resident workgroups, 0 one per tile)")
+    ap.add_argument("--least-workspace", action="store_true",
+                    help="the least workspace: connected configurations are evaluated row by row")
     ap.add_argument("--samples", default="psi", choices=["psi", "sector"],
                     help="psi: the batch is drawn from the network with the GPU unique-sample sampler "
                          "(1e12 draws, the batch size as buffer capacity); sector: uniform sector draws")
@@ -407,7 +409,7 @@ def main():
     eloc = torch.empty((B, 2), dtype=torch.float64, device=dev)
     energy = torch.empty(3, dtype=torch.float64, device=dev)
     grad = torch.empty(plan.n_params, dtype=torch.float64, device=dev)
-    plan.workspace(B)
+    plan.workspace(B, least=args.least_workspace)
     if args.tune:
         # the tuner times its probe, which needs warm kernels
         plan.autotune(params, x[:64], force=True)
@@ -416,7 +418,7 @@ def main():
     log(f"K={K} G={H.G} entries/sample={plan.entries_per_sample} chunk={plan.chunk_samples} "
         f"dedup={plan.dedup} waves={kinfo['waves_per_block']} rows={kinfo['rows_per_block']} "
         f"resident={kinfo['resident']} tuned={kinfo['tuned']} "
-        f"workspace={plan.workspace_size(B) / 2**30:.2f} GiB")
+        f"workspace={plan.workspace()[1] / 2**30:.2f} GiB")
     if tune is not None and not tune["from_cache"]:
         log("autotune: " + ", ".join(f"{c['waves_per_block']}w/{c['rows_per_block']}r/dedup{int(c['dedup'])}/"
                                     f"S{c['chunk_samples']}/"

@@ -14,7 +14,8 @@
 //     fully masked (block, k step) pairs are neither stored nor multiplied;
 //   * the head produces the n conditional logits and the 4 phases; the
 //     per-row epilogue applies the Hamming-weight modifier (Eq. modifier),
-//     sums the log-sigmoids of free positions in FP64 and selects the phase.
+//     sums the log-sigmoids of free positions in FP64 (in the order that the
+//     prefix-shared forward adds them) and selects the phase.
 // A model with a separate phase network runs the same kernel twice over the
 // same rows: the modulus network (writes log|psi|) and the phase network
 // (dense layers over the first n-2 positions, a 4-row head; writes phi).
@@ -448,6 +449,16 @@ __device__ __forceinline__ void head_loop(typename Tr<P>::Acc& acc, const WBuf& 
   }
 }
 
+// v of the lane N above, within 16 lanes (past them 0).
+template <int N>
+__device__ __forceinline__ double lane_above(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const int lo = (int)(unsigned)u, hi = (int)(unsigned)(u >> 32);
+  const unsigned a = (unsigned)__builtin_amdgcn_update_dpp(0, lo, 0x100 + N, 0xF, 0xF, true);
+  const unsigned b = (unsigned)__builtin_amdgcn_update_dpp(0, hi, 0x100 + N, 0xF, 0xF, true);
+  return __longlong_as_double((long long)((unsigned long long)b << 32 | a));
+}
+
 template <typename S>
 __device__ __forceinline__ S softplus(S z) {
   S a = z > S(0) ? z : -z;
@@ -735,7 +746,9 @@ __device__ __forceinline__ void fwd_tile(const Geom& g, const uint4* __restrict_
 
   // ------------------------------------------------------------ row epilogue
   constexpr int TPR = NT / M >= 1 ? NT / M : 1;
-  const int row = tid / TPR, sub = tid % TPR;
+  int et = tid;   // opaque: the epilogue's addresses are formed here and not held (spilled) through the layers
+  asm volatile("" : "+v"(et));
+  const int row = et / TPR, sub = et % TPR;
   if (row < M) {
     const S* hb = blds;
     const uint64_t y = ylds[row * W];
@@ -746,7 +759,6 @@ __device__ __forceinline__ void fwd_tile(const Geom& g, const uint4* __restrict_
       for (int p = 1; p < ksplit; ++p) v += stage[((long)p * M + row) * SP + col];
       return v + hb[col];
     };
-    double sum = 0.0;
     int bad = 0;
     const uint64_t sp0 = g.spin_pos[0], sp1 = g.spin_pos[1];
     const uint64_t sp0h = W == 2 ? g.spin_pos_hi[0] : 0ull, sp1h = W == 2 ? g.spin_pos_hi[1] : 0ull;
@@ -799,26 +811,62 @@ __device__ __forceinline__ void fwd_tile(const Geom& g, const uint4* __restrict_
       }
       return;
     }
-    for (int t = sub; t < g.n; t += TPR) {
-      const S o = head_out(t);
-      const int sp = spin(t);   // spin of the qubit at position t
-      const int bit = ybit(t);
-      bool fr = true;
-      if (constrained) {
-        int c, rem;
-        spin_counts(t, sp, c, rem);
-        const int ns = sp ? g.n_dn : g.n_up;
-        const bool f0 = c >= ns, f1 = c + rem < ns;
-        bad |= (f0 && bit) || (f1 && !bit);
-        fr = !(f0 || f1);
+    // Added in the order of sum_lanes.  Up to that many lanes a row: lane sub
+    // holds sums sub, sub + TPR, ..., a term of each at a time.  More: the terms
+    // change lanes through LDS, in the logits' places (a row's lanes are
+    // neighbours in one wave).  200,000 rows at 60 qubits, one sum per lane before:
+    // L = 1, 64 units, FP64 185 us (190), L = 3, 512 units, BF16 weights 392 (388),
+    // L = 4, 1024 units 1,390 (1,391).
+    constexpr int NS = sum_lanes(P), HELD = NS > TPR ? NS / TPR : 1, MET = NS < TPR ? NS : TPR;
+    double part[HELD] = {};
+    S* lsig = stage + (long)row * SP;
+    for (int t0 = sub; t0 < g.n; t0 += TPR * HELD) {
+#pragma unroll
+      for (int k = 0; k < HELD; ++k) {
+        const bool in = HELD == 1 || t0 + TPR * k < g.n;
+        const int t = in ? t0 + TPR * k : t0;
+        const S o = head_out(t);
+        const int sp = spin(t);   // spin of the qubit at position t
+        const int bit = ybit(t);
+        bool fr = in;
+        if (constrained) {
+          int c, rem;
+          spin_counts(t, sp, c, rem);
+          const int ns = sp ? g.n_dn : g.n_up;
+          const bool f0 = c >= ns, f1 = c + rem < ns;
+          bad |= (f0 && bit) || (f1 && !bit);
+          fr = in && !(f0 || f1);
+        }
+        const S v = fr ? softplus<S>(bit ? -o : o) : S(0);
+        if constexpr (TPR <= NS) part[k] -= (double)v;
+        else lsig[t] = v;
       }
-      if (fr) sum -= (double)softplus<S>(bit ? -o : o);
+    }
+    if constexpr (TPR > NS) {
+      __builtin_amdgcn_wave_barrier();
+      if (sub < NS)
+        for (int t0 = sub; t0 < g.n; t0 += 4 * NS) {
+          S v[4];                                // (in flight together)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int t = t0 + NS * i;
+            const S x = lsig[t < g.n ? t : 0];
+            v[i] = t < g.n ? x : S(0);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) part[0] -= (double)v[i];
+        }
     }
 #pragma unroll
-    for (int off = TPR / 2; off >= 1; off >>= 1) {
-      sum += __shfl_xor(sum, off);
-      bad |= __shfl_xor(bad, off);
-    }
+    for (int off = HELD / 2; off >= 1; off >>= 1)
+#pragma unroll
+      for (int k = 0; k < off; ++k) part[k] += part[k + off];
+    if constexpr (MET >= 16) part[0] += lane_above<8>(part[0]);
+    if constexpr (MET >= 8) part[0] += lane_above<4>(part[0]);
+    if constexpr (MET >= 4) part[0] += lane_above<2>(part[0]);
+    if constexpr (MET >= 2) part[0] += lane_above<1>(part[0]);
+    const double sum = part[0];
+    bad = (__ballot(bad) >> (et & 63 & ~(TPR - 1)) & (~0ull >> (64 - TPR))) != 0;
     if (sub == 0 && grow < count) {
       const double la = bad ? -INFINITY : 0.5 * sum;
       if (g.net_kind == 1) {

@@ -21,8 +21,9 @@
 // Each pre-activation is the same chain of MFMAs in the same k order as in the
 // row-by-row kernel (a state is a chain interrupted at a block boundary and
 // carried in the accumulator's own type; the head's k slices are carried as
-// the sum of the finished slices and the slice in progress), so the logits
-// and phases are that kernel's, bit for bit.
+// the sum of the finished slices and the slice in progress), and both kernels
+// add the log-sigmoids in one order, so log|psi| and phi are that kernel's,
+// bit for bit.
 //
 // A workgroup of eight waves walks its own segment of rows depth first, a tile
 // of M nodes at a time, and keeps two tiles of states per level, so states need
@@ -296,8 +297,8 @@ __device__ __forceinline__ int common_prefix(const uint64_t* x, int r, int n) {
 }
 
 // Units of one level's state: (L-1) layers of the units past the
-// cut, the head's finished slices and its slice in progress (per node follow the sum of
-// its log-sigmoids and the contradiction flag).
+// cut, the head's finished slices and its slice in progress (per node follow the sums of
+// its log-sigmoids).
 template <int P>
 __host__ __device__ inline long long state_units(const Geom& g, int cb) {
   return ((long long)(g.L - 1) * (g.NB - cb) + 2LL * g.NHB) * Kind<P>::TB;
@@ -353,9 +354,11 @@ struct TileJob {
   int place;
 };
 
-template <int P, int W, int MB>
+// early(): loads requested before the head's products, which hide their latency.
+template <int P, int W, int MB, class Early>
 __device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W, MB>& t, Weights wb,
-                                           const typename Kind<P>::S* biases, int ksplit, int wv, const TileJob& jb) {
+                                           const typename Kind<P>::S* biases, int ksplit, int wv, const TileJob& jb,
+                                           Early early) {
   using T = Kind<P>;
   using Acc = typename T::Acc;
   using S = typename T::S;
@@ -452,6 +455,7 @@ __device__ __forceinline__ void tile_units(const Geom& g, const TileLds<P, W, MB
     lds_barrier();
   }
 
+  early();
   // head: items of one head block and one row block
   const int hun = (L - 1) * sun, phun = (L - 1) * pun;
   for (int item = wv; item < MB * g.NHB; item += kWaves) {
@@ -570,9 +574,27 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
     const bool leaf = j == ta.nlev - 1;
     const char* pst = j > 0 ? scratch + ta.lev[j - 1].st : nullptr;
     char* st = scratch + lv.st;
+    // A node's state carries its log-sigmoids' sums: sum_lanes of them, one per
+    // thread of the node, so that rows are added in the row-by-row forward's order
+    // (400 samples at 64 qubits: 28.1 ms; with one sum per node, level by level,
+    // and other bits than row by row, 28.0).  1 stands for a contradiction: no sum
+    // is positive.
+    constexpr int NPW = 64 / M, NSUB = kWaves * NPW;
+    static_assert(NSUB == sum_lanes(P), "one sum per thread of a node");
+    auto subthread = [&](int tid) {                            // the sum of the level's first position is the first wave's
+      return (lv.ta + wv * NPW + (NPW > 1 ? (tid & 63) / M : 0)) & (NSUB - 1);
+    };
+    double sum = 0.0;
     tile_units<P, W, 2>(g, t, wb, biases, ta.ksplit, wv,
                      TileJob{lv.ca, lv.cb, lv.eb, lv.ta, leaf ? (g.net_kind == 1 ? n : n + 4) : lv.tb, !leaf, pst,
-                             2 * M, st, 2 * M, half});
+                             2 * M, st, 2 * M, half},
+                     [&] {
+                       const int tid = thread_index();
+                       if (j > 0)
+                         sum = ((const double*)(pst + state_units<P>(g, lv.ca) * (2 * M) *
+                                                          (long long)sizeof(S)))[subthread(tid) * (2 * M) +
+                                                                                 t.pidx[tid % M]];
+                     });
 
     // ------------------------------------------------- log-sigmoids, phase
     // A lane takes a node and a wave every eighth position (FP64, whose tiles
@@ -581,21 +603,16 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
     // 190 vector instructions a position and node 135 are left, 117 of them
     // log1pf.  (With a node's positions on eight lanes: 400 samples at 64
     // qubits, L = 3, 512 units, 31.4 ms, now 29.9.)
-    constexpr int NPW = 64 / M, NSUB = kWaves * NPW;
-    const int tid = thread_index(), m = tid % M, sub = wv * NPW + (NPW > 1 ? (tid & 63) / M : 0);
-    double2 up = make_double2(0.0, 0.0);                       // what the parent has summed
-    if (tid < M && j > 0)
-      up = ((const double2*)(pst + state_units<P>(g, lv.ca) * (2 * M) * (long long)sizeof(S)))[t.pidx[m]];
+    const int tid = thread_index(), m = tid % M, sub = subthread(tid);
     const uint64_t y = t.ylds[m * W], yh = W == 2 ? t.ylds[m * W + 1] : 0ull;
     auto bit = [&](int q) -> int { return (int)(((q < 64 ? y : yh) >> (q & 63)) & 1ull); };
     auto out = [&](int q) { return t.stage[m * t.stage_ld + q - lv.ta] + t.hbl[q - lv.ta]; };
     const bool constrained = g.n_up >= 0 && g.n_dn >= 0;
-    double sum = 0.0;
-    int bad = 0;
     uint64_t ahead = 0;                                        // brings the next tile's rows into L2
     if (leaf && wv == kWaves - 1 && row0 + M + m < rows) ahead = ta.x[(row0 + M + m) * W];
     const int tend = leaf ? n : lv.tb;
-    for (int q = lv.ta + sub; q < tend; q += NSUB) {
+    int bad = sum > 0.0;
+    for (int q = lv.ta + ((sub - lv.ta) & (NSUB - 1)); q < tend; q += NSUB) {
       const S o = out(q);
       const int b = bit(q);
       bool f0 = false, f1 = false;
@@ -604,30 +621,28 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
       if (!(f0 || f1)) sum -= (double)softplus<S>(b ? -o : o);
     }
     asm volatile("" ::"v"(ahead));
-    // the partial sums, in the place of the activations: none is positive, so 1 stands for a contradiction
-    double* part = (double*)t.act;
-    part[sub * M + m] = bad ? 1.0 : sum;
+    if (bad) sum = 1.0;
+    if (!leaf) {
+      ((double*)(st + state_units<P>(g, lv.cb) * (2 * M) * (long long)sizeof(S)))[sub * (2 * M) + half + m] = sum;
+      return;
+    }
+    double* part = (double*)t.act;                             // in the place of the activations
+    part[sub * M + m] = sum;
     lds_barrier();
-    if (tid < M) {
+    if (tid < M && m < c) {
       double v[NSUB];
 #pragma unroll
       for (int i = 0; i < NSUB; ++i) v[i] = part[i * M + m];
-      bad = up.y != 0.0;
+      bad = 0;
 #pragma unroll
       for (int i = 0; i < NSUB; ++i) bad |= v[i] > 0.0;
 #pragma unroll
       for (int off = NSUB / 2; off >= 1; off >>= 1)
 #pragma unroll
         for (int i = 0; i < off; ++i) v[i] += v[i + off];
-      sum = v[0] + up.x;
-      if (!leaf) {
-        ((double2*)(st + state_units<P>(g, lv.cb) * (2 * M) * (long long)sizeof(S)))[half + m] =
-            make_double2(sum, bad ? 1.0 : 0.0);
-      } else if (m < c) {
-        const double la = bad ? -INFINITY : 0.5 * sum;
-        if (g.net_kind == 1) ta.out[2 * (row0 + m)] = la;
-        else ((double2*)ta.out)[row0 + m] = make_double2(la, (double)out(n + 2 * bit(n - 2) + bit(n - 1)));
-      }
+      const double la = bad ? -INFINITY : 0.5 * v[0];
+      if (g.net_kind == 1) ta.out[2 * (row0 + m)] = la;
+      else ((double2*)ta.out)[row0 + m] = make_double2(la, (double)out(n + 2 * bit(n - 2) + bit(n - 1)));
     }
   };
 
@@ -786,7 +801,8 @@ __global__ __launch_bounds__(kThreads, 4) void sample_units(Geom g, StepArgs sa)
     lds_barrier();
     tile_units<P, W, MB>(g, t, wb, biases, sa.ksplit, wv,
                      TileJob{sa.ca, sa.cb, sa.eb, sa.t < 0 ? 0 : sa.t, sa.t < 0 ? 0 : sa.t + 1, sa.t < 0, sa.pst,
-                             sa.nodes, sa.st, sa.nodes, (int)r0});
+                             sa.nodes, sa.st, sa.nodes, (int)r0},
+                     [] {});
     if (sa.t >= 0 && tid < M && r0 + tid < rows) {
       const uint64_t y = t.ylds[tid * W], yh = W == 2 ? t.ylds[tid * W + 1] : 0ull;
       bool f0 = false, f1 = false;
@@ -834,7 +850,7 @@ bool plan_levels(const Geom& g, TreePlan& t) {
     while (tb < d && prefix_of_class(g, tb) <= cb * T::TB) ++tb;
     lv.tb = tb;
     lv.st = bytes;
-    bytes += state_units<P>(g, cb) * 2 * M * (long long)sizeof(typename T::S) + 2 * M * 16LL;
+    bytes += state_units<P>(g, cb) * 2 * M * (long long)sizeof(typename T::S) + 2LL * M * sum_lanes(P) * 8;
     ca = cb;
     ta = tb;
   }

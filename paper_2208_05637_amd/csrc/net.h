@@ -55,6 +55,12 @@ struct Geom {
   long long n_params;
 };
 
+// log|psi| is half the sum of the positions' log-sigmoids, added in FP64 in one
+// order by every forward and every tile shape, so that a configuration's value
+// does not depend on the one it gets: position t goes to sum t mod sum_lanes,
+// ascending, and the sums meet in a tree of halves.
+constexpr int sum_lanes(int prec) { return prec == P_F64 ? 16 : 8; }
+
 // Index into poff of the phase network's layer-l weight (l = 1..L; its bias
 // follows) and of the phase head's weight (its bias follows).
 __host__ __device__ inline int poff_phase_layer(const Geom& g, int l) { return 2 * g.L + 2 + 2 * (l - 1); }
