@@ -557,14 +557,7 @@ __global__ __launch_bounds__(kThreads, 4) void tree_forward(Geom g, TreeArgs ta)
     rows = c < rows ? c : rows;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && ta.prof_slot) *ta.prof_slot = rows;
-  // Segments repeat the upper levels' first tiles, so there are few: one per
-  // workgroup up to 3,072 rows each, else about four, of at most 16,384 rows
-  // (four from 1,024 rows on: a training step at 24 qubits, 1,668 rows per
-  // workgroup, 1.86 ms instead of 1.73; at 28 qubits, 2,100 rows, 2.37 of 2.25).
-  long long seg = (rows + gridDim.x - 1) / gridDim.x;
-  if (seg > 3072) seg = (seg + 3) / 4;
-  seg = seg > 16384 ? 16384 : (seg + M - 1) / M * M;
-  if (seg < M) seg = M;
+  const long long seg = tree_segment(rows, gridDim.x, M);
   const long long nseg = (rows + seg - 1) / seg;
 
   // One tile of c nodes of level j, at nodes half .. of the level's state (rows

@@ -211,6 +211,8 @@ static void grid_for(const nqs_ham* h, int64_t S, int ngroups, int& R, int& gper
   R = (ngroups + gper - 1) / gper;
 }
 
+static int tree_grid_of(const nqs_plan* p);
+
 static WsLayout layout(const nqs_plan* p, int64_t B) {
   WsLayout L{};
   size_t o = 0;
@@ -255,24 +257,56 @@ static WsLayout layout(const nqs_plan* p, int64_t B) {
   if (p->tree) {
     L.issued = take((size_t)kProfSlots * 8);
     L.tree = o;
-    // two workgroups per CU, and no more than the chunk has smallest segments
-    L.tree_grid = (int)std::min<int64_t>(2 * std::max(p->ctx->cu_count, 1), (p->EC + p->tp.rows - 1) / p->tp.rows);
+    L.tree_grid = tree_grid_of(p);
     take((size_t)L.tree_grid * p->tp.args.scratch_wg);
   }
   L.full = o;
   return L;
 }
 
-// A walk down the tree takes a handful of tiles one after the other, 60 us and
-// more however few the rows; row by row they are one wave of tiles over the
-// CUs.  So rows that the row-by-row forward does in about 100 us stay with it
-// (12 qubits, FP64, 64 units, 30,000 rows: 9 us against 86).  Rates: what the
-// row-by-row kernels reach, per CU.
-static bool tree_pays(const nqs_plan* p, int64_t most_rows) {
-  const double rate = (p->g.prec == P_F64 ? 60e12 : p->g.prec == P_F32 ? 130e12 : 1100e12) / 256;
-  const double rows = forward_rows_per_block(p->g.prec, p->g.h);
-  const double waves = std::ceil((double)most_rows / (rows * std::max(p->ctx->cu_count, 1)));
-  return p->levels && waves * (8e-6 + rows * p->flops_exec_row / rate) > 100e-6;
+// Whether `rows` connected configurations are faster down the prefix tree, on
+// `grid` workgroups, than row by row: what the two take, in us, from how their
+// work falls into tiles.  The row-by-row kernel takes waves of tiles over the
+// CUs.  A tree workgroup takes one tile after the other, at least one of each
+// level and at 1024 units 50 us each, so it needs several tiles of rows to gain:
+// 20,000 rows at 16 qubits, L = 4, 1024 units, BF16 weights, take 227 us row by
+// row and 463 down the tree, 399,000 rows at 40 qubits 2,670 and 1,440; with few
+// products to share (24 qubits, L = 1, 64 units, FP64) 400,000 rows 231 and 283.
+// How often rows share their upper nodes is known on the device only: in
+// molecules' lists the more, the more qubits.  The costs are fitted to 632 timed
+// pairs, 41 networks at 10 to 52 qubits and 2,000 to 2 million rows; going by them
+// loses 0.2% of the faster forward's time on average, 19% at the worst point.
+static bool tree_pays(const nqs_plan* p, int64_t rows, int grid) {
+  if (!p->levels || rows <= 0 || grid <= 0) return false;
+  // us per wave of tiles and per tile, each with their layers, then per million
+  // MFMA flops (of a tree tile also beyond 512 units) and per 1,000 log-sigmoids
+  struct Cost { double wave, wave_layer, flop, sig, tile, tile_layer, tree_flop, tree_flop_wide, tree_sig; };
+  static const Cost costs[] = {{2.1, 1.8, 3.9, 2.7, 0.7, 0.16, 4.2, 2.7, 3.3},       // P_F64
+                               {0.4, 4.4, 1.78, 1.64, 1.3, 0.0, 1.95, 2.1, 1.26},    // P_F32
+                               {5.0, 3.6, 0.171, 1.25, 0.44, 0.34, 0.27, 0.33, 1.4}, // P_BF16
+                               {9.2, 0.0, 0.221, 0.82, 0.82, 0.13, 0.187, 0.27, 1.5},    // P_BF16X3
+                               {7.5, 1.4, 0.173, 1.1, 1.2, 0.18, 0.215, 0.27, 1.1}};     // P_BF16W
+  const Cost& c = costs[p->g.prec];
+  const TreeArgs& t = p->tp.args;
+  const int cus = std::max(p->ctx->cu_count, 1), tile = forward_rows_per_block(p->g.prec, p->g.h), M = p->tp.rows;
+  const double waves = std::ceil((double)rows / ((double)tile * cus));
+  const double row_us = 7.0 + waves * (c.wave + c.wave_layer * p->g.L + tile * p->g.n * 1e-3 * c.sig +
+                                       tile * (p->flops_exec_row - p->flops_exec_phase_row) * 1e-6 * c.flop);
+  // the kernel's cut of the rows into segments, a workgroup's tiles of each level
+  const int64_t seg = tree_segment(rows, grid, M), nseg = (rows + seg - 1) / seg;
+  const double turns = (double)((nseg + grid - 1) / grid), leaves = (double)(seg / M);
+  const double uppers = 1.0 + std::max(0.0, 1.0 - p->g.n / 96.0) * (leaves - 1.0);
+  double walk = 0.0;
+  for (int j = 0; j < t.nlev; ++j)
+    walk += (j + 1 < t.nlev ? uppers : leaves) *
+            (c.tile + c.tile_layer * p->g.L + M * (t.lev[j].tb - t.lev[j].ta) * 1e-3 * c.tree_sig +
+             (double)t.lev[j].flops * 1e-6 * (p->g.h > 512 ? c.tree_flop_wide : c.tree_flop));
+  // (two workgroups on a CU slow each other)
+  return 35.0 + (nseg > cus ? 1.5 : 1.0) * turns * walk < row_us;
+}
+static int tree_grid_of(const nqs_plan* p) {
+  // two workgroups per CU, and no more than the chunk has smallest segments
+  return (int)std::min<int64_t>(2 * std::max(p->ctx->cu_count, 1), (p->EC + p->tp.rows - 1) / p->tp.rows);
 }
 
 // With `room` bytes for the tree's part there may be states for fewer
@@ -879,7 +913,7 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
     p->flops_exec_row = 2.0 * g.TB * g.KSTEP * (mult1 * (double)fr1 + mult * (double)fr) + p->flops_exec_phase_row;
   }
   p->levels = tree_plan(p->g, p->tp);
-  p->tree = tree_pays(p, p->EC);
+  p->tree = p->levels && tree_pays(p, p->EC, tree_grid_of(p));
   *out = p;
   return NQS_OK;
 }
@@ -1008,7 +1042,7 @@ static void forward_net(const nqs_plan* p, const void* packed, const uint64_t* x
 }
 
 // Whether rows of connected configurations (their bound) go down the prefix tree.
-static bool by_tree(const nqs_plan* p, const WsLayout& L, long long bound) { return L.tree_grid && tree_pays(p, bound); }
+static bool by_tree(const nqs_plan* p, const WsLayout& L, long long bound) { return tree_pays(p, bound, L.tree_grid); }
 
 // The same of connected configurations in the enumeration's order, down their
 // prefix tree.

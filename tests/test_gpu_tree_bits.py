@@ -1,5 +1,5 @@
 """The two forwards of the connected configurations give equal bits: local
-energies down the prefix tree (a full workspace, and half of its states) and row
+energies down the prefix tree (a full workspace, and part of its states) and row
 by row (the least workspace) are the same doubles, for every kind, workgroup
 shape, word count, with and without hash tables, chunk by chunk and in one.  That
 the full workspace takes the tree and the least does not is read off the matrix
@@ -115,10 +115,10 @@ def test_same_bits(nqs, n, prec, h, L, G, phase, sector, B):
         plan.configure(waves_per_block=waves, rows_per_block=rows)
         rowwise, f0 = _eloc(plan, params, x, least)
         tree, f1 = _eloc(plan, params, x, full)
-        half, f2 = _eloc(plan, params, x, least + (full - least) // 2)
+        part, f2 = _eloc(plan, params, x, least + int(0.85 * (full - least)))
         assert f1 != f0 and f2 != f0                           # other matrix operations: the tree ran
         assert bool(torch.isfinite(rowwise).all())
-        assert torch.equal(tree, rowwise) and torch.equal(half, rowwise)
+        assert torch.equal(tree, rowwise) and torch.equal(part, rowwise)
 
 
 @pytest.mark.parametrize("n,prec,h,L,phase,sector", [
