@@ -841,7 +841,7 @@ nqs_status nqs_plan_create(nqs_ctx* ctx, const nqs_ham* ham, const nqs_net_desc*
   }
   const int ngroups = G - gfirst;
   grid_for(ham, p->S, ngroups, p->R, p->gper);
-  // count arrays sized for every chunk the autotuner may pick (S0, S0/2)
+  // count arrays sized for the chunks the autotuner may pick (S0, S0/2); set_chunk fits the others in
   {
     int r2 = 1, gp2 = 0;
     const int64_t half = std::max<int64_t>(1, p->S0 / 2);
@@ -1488,6 +1488,14 @@ void set_chunk(nqs_plan* p, int64_t S) {
   const int gfirst = ham_has_diag(p->ham) ? 1 : 0;
   p->S = S;
   grid_for(p->ham, S, G - gfirst, p->R, p->gper);
+  // a chunk between the created one and its half can have more ranges than the
+  // count arrays, sized for these two, have room for (179,200 created: 3 ranges
+  // for 174,572 samples, 2 for 179,200)
+  if (S * p->R > p->SRcap) {
+    const int r = (int)(p->SRcap / S);
+    p->gper = (G - gfirst + r - 1) / r;
+    p->R = (G - gfirst + p->gper - 1) / p->gper;
+  }
 }
 }  // namespace
 
