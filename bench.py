@@ -101,6 +101,26 @@ def measured_traffic(workload, prec, waves, rows):
         return None
 
 
+def forward_rates(pr):
+    """Rates of a profile's forwards: MFMA work issued, and the work of the network row by row over the same time
+    (above the card's peak where the prefix tree shares it)."""
+    s = max(pr["forward_ms"], 1e-9) / 1e3
+    return {"mfma_issued_tflops": pr["forward_flops_executed"] / s / 1e12,
+            "row_by_row_equivalent_tflops": pr["forward_flops"] / s / 1e12}
+
+
+def down_the_tree(nqs, plan_of_one, params, x, pr):
+    """Whether the profiled connected configurations went down the prefix tree: their matrix operations per row are
+    not those of one sample's with the least workspace, which go row by row."""
+    plan_of_one.workspace(least=True)
+    plan_of_one.profile(True)
+    nqs.local_energy(plan_of_one, params, x[:1])
+    one = plan_of_one.profile_read()
+    plan_of_one.profile(False)
+    per_row = one["forward_flops_executed"] / one["forward_rows"]
+    return abs(pr["forward_flops_executed"] / (max(pr["forward_rows"], 1) * per_row) - 1.0) > 1e-9
+
+
 # Bit strings of two words: 76 qubits, the size of the paper's largest system
 # (38 spatial orbitals, 19 + 19 electrons).  The integrals' two-electron part
 # is cut below 2.5e-5, which leaves about as many Pauli strings as the
@@ -149,15 +169,16 @@ def wide_76(nqs, ctx, cfg, prec, count):
            "sampler_ms": s0.elapsed_time(s1),
            "entries_per_sample_bound": pl.entries_per_sample, "entries": entries, "dedup_ratio": ratio,
            "chunk_samples": pl.chunk_samples, "dedup": pl.dedup, "forward_rows": pr["forward_rows"],
-           "forward_waves_per_block": pl.kernel_info()["waves_per_block"],
+           "row_kernel_waves_per_block": pl.kernel_info()["waves_per_block"],
            "samples_terms_per_s": count * H.K / (pr["eloc_ms"] / 1e3),
            "connected_configs_per_s": pr["forward_rows"] / (pr["eloc_ms"] / 1e3),
-           "forward_tflops": pr["forward_flops"] / (pr["forward_ms"] / 1e3) / 1e12,
+           **forward_rates(pr),
            "forward_ms_per_launch": pr["forward_ms"] / max(pr["forward_launches"], 1),
            "energy_mean": float(np.mean(el[:, 0])), "device_status": status}
     log(f"76 qubits ({H.K} strings, {count} samples, {entries} entries, dedup ratio {ratio:.3f}, dedup "
         f"{'on' if pl.dedup else 'off'}): {res['samples_terms_per_s']:.3e} samples*terms/s, "
-        f"{res['forward_tflops']:.1f} TFLOP/s")
+        f"{res['mfma_issued_tflops']:.1f} TFLOP/s MFMA issued, {res['row_by_row_equivalent_tflops']:.1f} TFLOP/s of "
+        f"row-by-row work")
     return res
 
 
@@ -472,12 +493,12 @@ def main():
     issued = prof["forward_flops_executed"] / (prof["forward_ms"] / 1e3) / 1e12
     peak = PEAKS_TFLOPS[prec]
     log(f"forward kernel: {prof['forward_launches']} launches, {fwd_ms_launch:.2f} ms/launch, "
-        f"{achieved:.1f} TFLOP/s algorithmic, {issued:.1f} TFLOP/s MFMA issued (peak {peak})")
+        f"{achieved:.1f} TFLOP/s of row-by-row work, {issued:.1f} TFLOP/s MFMA issued (peak {peak})")
     el_main = eloc.cpu().numpy()
     E_main = energy.cpu().numpy()
     # down the prefix tree fewer products are issued than the network has row by row: the rate of
     # those that are issued is the kernel's, and the row-by-row work over the same time goes beside it
-    shared = prof["forward_flops_executed"] < prof["forward_flops"]
+    shared = down_the_tree(nqs, mk(prec, 1), params, x, prof)
     bpr = (tree_traffic(args.workload, prec) if shared
            else measured_traffic(args.workload, prec, kinfo["waves_per_block"], kinfo["rows_per_block"]))
     rate = issued if shared else achieved
@@ -508,6 +529,7 @@ def main():
             "eloc_ms": eloc_ms,
             "chunk_samples": plan.chunk_samples,
             "dedup": plan.dedup,
+            # the row-by-row kernel's workgroups: the samples' forward, and the k slices of the prefix tree's head
             "forward_waves_per_block": kinfo["waves_per_block"],
             "forward_rows_per_block": kinfo["rows_per_block"],
             "forward_resident_grid": kinfo["resident"],
@@ -615,15 +637,16 @@ def main():
             pr = pl.profile_read()
             pl.profile(False)
             side[p] = dict(eloc=el.cpu().numpy(), value=P * K / (pr["eloc_ms"] / 1e3),
-                           tflops=pr["forward_flops"] / (pr["forward_ms"] / 1e3) / 1e12,
+                           rates=forward_rates(pr),
                            waves=pl.kernel_info()["waves_per_block"])
             log(f"{p} path on {P} samples: {side[p]['value']:.3e} samples*terms/s, "
-                f"{side[p]['tflops']:.1f} TFLOP/s")
+                f"{side[p]['rates']['mfma_issued_tflops']:.1f} TFLOP/s MFMA issued, "
+                f"{side[p]['rates']['row_by_row_equivalent_tflops']:.1f} TFLOP/s of row-by-row work")
             del pl
         Ep = {p: math.fsum(wp * d["eloc"][:, 0]) / math.fsum(wp) for p, d in side.items()}
         ref = Ep["fp64"]
         out["paths_on_prefix"] = {"prefix_samples": P, **{
-            p: {"samples_terms_per_s": d["value"], "forward_tflops": d["tflops"], "waves_per_block": d["waves"],
+            p: {"samples_terms_per_s": d["value"], **d["rates"], "row_kernel_waves_per_block": d["waves"],
                 "energy_prefix": Ep[p], "abs_dE_vs_fp64_gpu": abs(Ep[p] - ref)} for p, d in side.items()}}
         out["speedup_vs_fp32_path"] = side[prec]["value"] / side["fp32"]["value"]
         out["abs_dE_prefix_vs_fp64"] = abs(Ep[prec] - ref)
@@ -680,7 +703,7 @@ def main():
                 pl.profile(False)
                 ev = math.fsum(wp * el[:, 0].cpu().numpy()) / math.fsum(wp)
                 var[name] = {"samples_terms_per_s": P * K / (pr["eloc_ms"] / 1e3),
-                             "forward_tflops": pr["forward_flops"] / (pr["forward_ms"] / 1e3) / 1e12,
+                             **forward_rates(pr),
                              "alg_flop_per_row": pr["forward_flops"] / max(pr["forward_rows"], 1),
                              "energy_prefix": ev}
                 log(f"variant {name}: {var[name]['samples_terms_per_s']:.3e} samples*terms/s")
