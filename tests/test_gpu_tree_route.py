@@ -71,3 +71,19 @@ def test_route(nqs, orbitals, layers, width, precision, phase, samples, tree):
         print(f"{n} qubits, L={layers}, {width} {precision}, {samples} samples: tree {f1 != f0}", flush=True)
         assert (f1 != f0) == tree
         assert torch.equal(e0, e1)
+
+
+@pytest.mark.parametrize("orbitals,cutoff,precision,chunk", [(12, 0.0, "bf16x3", 128), (38, 0.02, "bf16w", 32)])
+def test_tuned_plans_of_the_tuner_tests(nqs, orbitals, cutoff, precision, chunk):
+    """Two plans as the autotuner's tests use them (24 qubits; 76, of fewer strings there): their chunks go down the
+    tree, so the candidates' shapes differ by the head's k slices and no more."""
+    n, ne = 2 * orbitals, orbitals // 2
+    ctx = nqs.Context(0)
+    H = nqs.Hamiltonian.from_terms(hamiltonian(orbitals, 0, cutoff=cutoff)).upload(ctx)
+    params = torch.from_numpy(init_params(n, 2, 512, seed=5)).cuda()
+    x, _ = unique_with_counts(sector_samples(n, ne, ne, 2 * chunk, seed=4))
+    x = torch.from_numpy(np.resize(x, (2 * chunk,) + x.shape[1:]).view(np.int64)).cuda()
+    plan = nqs.Plan(ctx, H, 2, 512, ne, ne, precision, max_batch=2 * chunk, dedup="auto", chunk_samples=chunk)
+    e0, f0 = _flops(plan, params, x, plan.workspace_size(2 * chunk, least=True))
+    e1, f1 = _flops(plan, params, x, plan.workspace_size(2 * chunk))
+    assert f1 != f0 and torch.equal(e0, e1)
