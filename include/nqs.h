@@ -269,9 +269,10 @@ void       nqs_plan_destroy(nqs_plan* plan);
 nqs_status nqs_plan_configure(nqs_plan* plan, int waves_per_block, int rows_per_block, int dedup,
                               int64_t chunk_samples, int resident);
 
-/* Workgroup shape of the plan's connected-configuration forward: waves per
-   workgroup, configurations per workgroup, whether the plan was tuned, and
-   whether the forward runs a resident grid (each output may be NULL). */
+/* Workgroup shape of the plan's row-by-row forward: waves per workgroup,
+   configurations per workgroup, whether the plan was tuned, and whether it
+   runs a resident grid (each output may be NULL).  Connected configurations
+   that go down the prefix tree take only the head's k slices from it. */
 nqs_status nqs_plan_kernel_info(const nqs_plan* plan, int* waves_per_block, int* rows_per_block,
                                 int* tuned, int* resident);
 
@@ -291,7 +292,9 @@ nqs_status nqs_plan_kernel_info(const nqs_plan* plan, int* waves_per_block, int*
    plan unchanged, without timing or touching the device).  Every candidate
    computes the same local energies up to the forward's rounding (dedup,
    chunking and the grid change nothing; the two workgroup shapes split the
-   head's k sum differently).  Synchronises the
+   head's k sum differently).  Where the chunks go down the prefix tree the
+   shapes and grids take the same time but for the samples' own forward, and
+   which of them is kept is chance.  Synchronises the
    context's stream; not for use under graph capture.  d_ws must hold
    nqs_plan_workspace_size(plan, B) bytes.  report may be NULL.  With the
    environment variable NQS_TUNE_LOG set, each timed candidate is also
@@ -340,8 +343,9 @@ nqs_status nqs_tune_db_load(const char* path, int* n_loaded);
  */
 
 /* log psi for n configurations: d_out[2*i] = log|psi|, d_out[2*i+1] = phi,
-   computed by the connected-configuration forward kernel of the plan's
-   precision (-inf for psi = 0).  Sec. 4, the complex logarithm of f. */
+   computed by the row-by-row forward kernel of the plan's precision
+   (-inf for psi = 0); connected configurations get the same values from
+   either forward.  Sec. 4, the complex logarithm of f. */
 nqs_status nqs_log_psi(nqs_plan* plan, const float* d_params, const uint64_t* d_x, int64_t n,
                        double* d_out, void* d_ws, size_t ws_bytes);
 

@@ -203,7 +203,12 @@ struct SampleBufs {
 void launch_sample_init(uint64_t* x, int words, long long* cnt, long long n_draws, long long* d_u, hipStream_t s);
 // Children of the buffer's entries, and the new buffer of at most umax of them.
 // anc_in (nullptr: i), anc_out: a number per entry that its children inherit;
-// kept up to kFoldEntries entries.
+// kept up to kFoldEntries entries.  Beyond, the whole network is evaluated at
+// every position and the elimination takes ten launches: each workgroup of the
+// one-launch elimination reads all counts, which grows with the square of the
+// buffer, and the walk's states take up to 16 KB an entry (1024 units, L = 4: 2 GiB at
+// the limit).  Drawing at 60 qubits with that network: 16.6 ms at 131,072 entries,
+// 61 ms at one more; at 24 qubits, 256 units, FP32: 2.1 and 7.9 ms.
 constexpr long long kFoldEntries = 131072;
 void launch_sample_step(const SampleBufs& b, long long umax, int t, int q, uint64_t seed, const int* anc_in,
                         int* anc_out, hipStream_t s);
