@@ -29,8 +29,8 @@
 // of M nodes at a time, and keeps two tiles of states per level, so states need
 // room per workgroup and not for every node of the call.  Two workgroups share
 // a CU and fill each other's barriers (one alone takes 1.26 times as long).  At
-// 60 qubits and 1024 units the matrix cores are busy 35% of the time, beside
-// state traffic of 3.2 TB/s past L2; at 64 qubits and 512 units 20%, where the
+// 60 qubits and 1024 units the matrix cores are busy 33% of the time, beside
+// state traffic of 3.5 TB/s past L2; at 64 qubits and 512 units 20%, where the
 // vector instructions of the conversions and the log-sigmoids take half of the
 // issue cycles and the activations' reads most of LDS's rate during the products.
 // Measured on 2,000 samples at 60 qubits, L = 4, 1024 units: 191 ms against
